@@ -11,6 +11,8 @@
 #include "kernels.h"
 #include "seed_iter.h"
 
+#include <type_traits>
+
 namespace ovl {
 
 // ============================================================================
@@ -866,62 +868,142 @@ void launch_dov_psi(const double2* b, const double2* s, double2* psi, double a, 
     hipLaunchKernelGGL(k_dov_psi, dim3(nblk), dim3(kBlock), 0, st, b, s, psi, a, bm, Vt, partial);
 }
 
-// Y[j][e] = sum_{i < K} u_i^{j} r_i[e] for shifts j0 .. j0+jn-1 (jn <= JG) of
-// one source: every stored slot in turn (FP64 below ksw, FP32 from it, at
-// the slot base), through the device table of slot chunks, each output
-// written once.  The basis is read once per group of JG shifts.
-template <int JG>
-__global__ __launch_bounds__(kBlock) void k_materialize(char* const* __restrict__ chunks,
-                                                        size_t slot_bytes, int K, int ksw,
-                                                        const double2* __restrict__ W, int J,
-                                                        int j0, int jn, double2* __restrict__ Y,
-                                                        int64_t n12, int64_t eoff) {
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= n12) return;
-    double re[JG], im[JG];
-#pragma unroll
-    for (int q = 0; q < JG; ++q) re[q] = im[q] = 0.0;
-    // the slot bases come from a table in memory: the loads go through
-    // global address-space pointers (global, not flat, loads)
+// Y[j][e] = sum_{i < K} u_i^j r_i[e] for shifts j0 .. j0+jn-1 of one source:
+// a complex (shifts x slots) by (slots x elements) product in FP64, on the
+// FP64 matrix instruction (16 shifts x 16 elements, four slots a step; the
+// complex product is four real ones).  A wave takes 16 MT shifts and 16 NT
+// elements: a slot's element is loaded once for 16 MT shifts, the basis is
+// read once per 16 MT shifts, every Y is written once, and the next step's
+// operands are in flight while this step multiplies.  Slots below ksw hold
+// FP64, from ksw on FP32; a step's four slots lie in one slot chunk.
+// Bound: the FP64 matrix rate.  128 shifts x 446 slots at 16^4 (3.6e11 flop)
+// take 5.7 ms, 63 Tflop/s where a large FP64 matrix product reaches 71, with
+// 64 x 32 per wave (5.9 ms with 64 x 16 or 128 x 16); one thread per element
+// and 16 shifts a pass, on vector instructions, took 15.1 ms, and 6.3 ms
+// against 0.37 ms at 8^4, where it left most of the chip idle.  Two waves per
+// SIMD at least keep the accumulators in vector registers: with fewer the
+// compiler moves all of them to and from the accumulation registers every step.
+template <int MT, int NT>
+__global__ __launch_bounds__(kBlock, 2) void k_materialize(char* const* __restrict__ chunks,
+                                                           size_t slot_bytes, int K, int ksw,
+                                                           const double2* __restrict__ W, int J,
+                                                           int j0, int jn,
+                                                           double2* __restrict__ Y, int64_t n12,
+                                                           int64_t eoff, int ngrp) {
+    typedef double __attribute__((ext_vector_type(4))) D4;
     typedef double __attribute__((ext_vector_type(2))) D2;
     typedef float __attribute__((ext_vector_type(2))) F2;
-    for (int i = 0; i < K; ++i) {
-        const OVL_GLOBAL char* slot =
-            (const OVL_GLOBAL char*)chunks[i / kSlotChunk] + (size_t)(i % kSlotChunk) * slot_bytes;
-        double vr, vi;
-        if (i < ksw) {
-            const D2 v = ((const OVL_GLOBAL D2*)slot)[eoff + e];
-            vr = v.x;
-            vi = v.y;
-        } else {
-            const F2 v = ((const OVL_GLOBAL F2*)slot)[eoff + e];
-            vr = v.x;
-            vi = v.y;
-        }
-        const double2* wr = W + (size_t)i * J + j0;
+    static_assert(kSlotChunk % 4 == 0, "a step's slots lie in one chunk");
+    const int lane = (int)(threadIdx.x & 63), nn = lane & 15, kk = lane >> 4;
+    // the shift groups of one stretch of elements run side by side
+    const int grp = (int)blockIdx.x % ngrp;
+    const int64_t e =
+        ((int64_t)(blockIdx.x / ngrp) * (kBlock / 64) + (threadIdx.x >> 6)) * (16 * NT) + nn;
+    const int jb = grp * 16 * MT;  // first shift of the group, from j0
+    D4 re[MT][NT], im[MT][NT];
 #pragma unroll
-        for (int q = 0; q < JG; ++q) {
-            if (q < jn) {
-                const double2 u = wr[q];
-                re[q] += u.x * vr - u.y * vi;
-                im[q] += u.x * vi + u.y * vr;
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) re[m][q] = im[m][q] = D4{0.0, 0.0, 0.0, 0.0};
+    // this lane's shift of each tile, clamped to the chunk
+    int jm[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) jm[m] = j0 + (jb + 16 * m + nn < jn ? jb + 16 * m + nn : jn - 1);
+    struct Step {
+        D2 v[NT], u[MT];
+    };
+    // steps [a, b) (in slots, a a multiple of 4) of one storage kind: 0 all
+    // FP64, 1 all FP32, 2 either
+    auto steps = [&](auto kind, int a, int b) {
+        constexpr int KIND = decltype(kind)::value;
+        auto load = [&](int i0, Step& t) {
+            const int i = i0 + kk < K ? i0 + kk : K - 1;
+            const OVL_GLOBAL char* slot = (const OVL_GLOBAL char*)chunks[i0 / kSlotChunk] +
+                                          (size_t)(i % kSlotChunk) * slot_bytes;
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                if (KIND == 0 || (KIND == 2 && i < ksw)) {
+                    t.v[q] = ((const OVL_GLOBAL D2*)slot)[eoff + e + 16 * q];
+                } else {
+                    const F2 f = ((const OVL_GLOBAL F2*)slot)[eoff + e + 16 * q];
+                    t.v[q] = D2{(double)f.x, (double)f.y};
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+                t.u[m] = ((const OVL_GLOBAL D2*)W)[(int64_t)i * J + jm[m]];
+        };
+        if (a >= b) return;
+        Step t;
+        load(a, t);
+#pragma unroll 1
+        for (int i0 = a; i0 < b; i0 += 4) {
+            const Step c = t;
+            // in flight during this step's products (the scheduler would sink them)
+            load(i0 + 4 < b ? i0 + 4 : i0, t);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                // slots beyond K (shifts beyond the chunk are not stored)
+                const bool on = i0 + kk < K;
+                const double ur = on ? c.u[m].x : 0.0, ui = on ? c.u[m].y : 0.0;
+#pragma unroll
+                for (int q = 0; q < NT; ++q) {
+                    re[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ur, c.v[q].x, re[m][q], 0, 0, 0);
+                    im[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ur, c.v[q].y, im[m][q], 0, 0, 0);
+                }
+#pragma unroll
+                for (int q = 0; q < NT; ++q) {
+                    re[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ui, c.v[q].y, re[m][q], 0, 0, 0);
+                    im[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ui, c.v[q].x, im[m][q], 0, 0, 0);
+                }
             }
         }
+    };
+    const int k64 = ksw < K ? ksw : K;       // slots [0, k64) hold FP64
+    const int a64 = k64 == K ? 0 : k64 & ~3; // whole FP64 steps before FP32 begins
+    if (k64 == K) {
+        steps(std::integral_constant<int, 0>{}, 0, K);
+    } else {
+        steps(std::integral_constant<int, 0>{}, 0, a64);
+        const int m1 = k64 & 3 ? a64 + 4 : a64;  // a step of both kinds
+        steps(std::integral_constant<int, 2>{}, a64, m1 < K ? m1 : K);
+        steps(std::integral_constant<int, 1>{}, m1, K);
     }
+    // register r of lane l holds row l / 16 + 4 r (shift), column l % 16 (element)
 #pragma unroll
-    for (int q = 0; q < JG; ++q)
-        if (q < jn) Y[(size_t)q * n12 + e] = make_double2(re[q], im[q]);
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = jb + 16 * m + kk + 4 * r;
+            if (j < jn)
+#pragma unroll
+                for (int q = 0; q < NT; ++q)
+                    stc<double>(Y, (int64_t)j * n12 + e + 16 * q, mk<double>(re[m][q][r], im[m][q][r]));
+        }
 }
-constexpr int kMatGroup = 16;
 void launch_materialize(char* const* chunks, size_t slot_bytes, int K, int ksw, const double2* W,
                         int J, int j0, int jn, double2* Y, int64_t n12, int64_t eoff,
                         hipStream_t s) {
-    dim3 grid((unsigned)((n12 + kBlock - 1) / kBlock));
-    for (int q0 = 0; q0 < jn; q0 += kMatGroup) {
-        const int m = jn - q0 < kMatGroup ? jn - q0 : kMatGroup;
-        hipLaunchKernelGGL(k_materialize<kMatGroup>, grid, dim3(kBlock), 0, s, chunks, slot_bytes,
-                           K, ksw, W, J, j0 + q0, m, Y + (size_t)q0 * n12, n12, eoff);
+    // n12 = 12 Vt is a multiple of 768, so the tiles of 4 waves are whole
+    auto go = [&](auto M, auto N) {
+        constexpr int MT = decltype(M)::value, NT = decltype(N)::value;
+        const int ngrp = (jn + 16 * MT - 1) / (16 * MT);
+        const dim3 grid((unsigned)(n12 / (16 * NT * (kBlock / 64)) * ngrp));
+        hipLaunchKernelGGL((k_materialize<MT, NT>), grid, dim3(kBlock), 0, s, chunks, slot_bytes, K,
+                           ksw, W, J, j0, jn, Y, n12, eoff, ngrp);
+    };
+    if (K < 1) {  // no slot: the sums are empty
+        (void)hipMemsetAsync(Y, 0, (size_t)jn * n12 * sizeof(double2), s);
+        return;
     }
+    using std::integral_constant;
+    // the fewest padding rows.  Up to 16 shifts reading the basis bounds it;
+    // from there the products do, and 64 shifts x 32 elements a wave (128
+    // accumulator registers) reach 90% of the matrix rate (see above)
+    if (jn <= 16) go(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    else if (jn <= 32) go(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    else go(integral_constant<int, 4>{}, integral_constant<int, 2>{});
 }
 
 // Basis form, the whole sum in one pass over the stored slots: for source n
