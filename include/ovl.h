@@ -73,7 +73,8 @@ extern "C" {
                                context switches on its own residuals)                         */
 
 #define OVL_FORM_REFERENCE 0 /* per-shift solutions x_j kept in HBM, s = sum c_j x_j at the end */
-#define OVL_FORM_FUSED     1 /* per-shift directions p_j only; s accumulated in the same sweep  */
+#define OVL_FORM_FUSED     1 /* per-shift directions p_j only; s accumulated in the same sweep
+                                (both: one sweep per 16 iterations, over 16 residual buffers)   */
 #define OVL_FORM_BASIS     2 /* seed residuals r_k stored; s = sum_k h_k r_k from the scalars    */
 #define OVL_FORM_TWOPASS   3 /* as BASIS without storing the r_k: a second pass regenerates them
                                 bit for bit (deterministic reductions) and accumulates s       */
@@ -307,8 +308,9 @@ int ovl_bench_kernel(ovl_ctx* ctx, int32_t which, int32_t nrhs, int32_t reps,
  * since the last ovl_set_profiling(ctx, 1).  kclass:
  *   0 stencil FP64 (q = z_s p - H p with <r,q>,   1 the same in FP32
  *     ||q||^2 and ||r||^2)
- *   2 r and p update FP64 (one kernel)             3 the same in FP32
- *   4 r update with the shift sweep FP64           5 the same in FP32
+ *   2 r update FP64                                3 the same in FP32
+ *   4 shift sweep FP64 (fused and reference        5 the same in FP32
+ *     forms, one per 16 iterations)
  *   6 basis sum s = sum h_k r_k                    7 scalar kernels
  *   8 fused iteration FP64 (basis forms: r_k and   9 the same in FP32
  *     q_k = A r_k + beta q_{k-1} in one kernel)

@@ -66,12 +66,19 @@ template <typename R>
 void launch_wilson_jobs(const JobDesc* jobs, int njobs, const int* kdev, int total_blocks,
                         int variant, int lnk, hipStream_t s, hipEvent_t ev0 = nullptr,
                         hipEvent_t ev1 = nullptr);
-// K2: seed and shift scalars, shift bookkeeping, r update and p update or
-// sweep; reads the iteration index from kread and writes its successor to kwrite
+// K2: seed and shift scalars, shift bookkeeping, r update; reads the iteration
+// index from kread and writes its successor to kwrite
 template <typename R>
 void launch_iteration_update(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
-                             int vec_blocks_total, int form, int maxJ, hipStream_t s,
-                             hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                             int vec_blocks_total, hipStream_t s, hipEvent_t ev0 = nullptr,
+                             hipEvent_t ev1 = nullptr);
+// sweep forms, after every kSweep iterations: the shifted directions and the
+// sum (or the shifted solutions) advanced by all of them; kdev is the
+// iteration counter after the last one, units the largest sweep_units of a job
+template <typename R>
+void launch_sweep_jobs(const JobDesc* jobs, int njobs, const int* kdev, int units, int form,
+                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+int sweep_units(int64_t n12, int nsrc);
 // The fused one-kernel seed iteration of the basis forms (stencil.hip): kernel
 // k forms r_k and q_k = A r_k + beta q_{k-1} without the direction p, and
 // advances the shifts by iteration k-1; reads k from kread, writes k + 1 to

@@ -245,7 +245,9 @@ void launch_convert_64_to_32(const double2* a, float2* b, int64_t n, hipStream_t
 //   K2  alpha_k, beta_k (every block, from K1's partials), shifted pi_{k+1},
 //       alpha^j, beta^j, residual estimates and deactivation (blocks
 //       0..nslices-1 own one 256-shift slice each, one lane per shift), then
-//       r_{k+1} = r_k - alpha_k q_k, alone or with the shift sweep.
+//       r_{k+1} = r_k - alpha_k q_k.
+// The sweep forms add a third kernel after every kSweep iterations, which
+// advances the shifted directions and the sum by all of them (k_sweep_jobs).
 // Quantities written in iteration k live in parity (k&1) or mod-3 buffers, so
 // no block reads what another block of the same kernel writes:
 //   SrcState.rr[k&1] = ||r_k||^2, alpha[k&1], beta[k&1];
@@ -265,13 +267,13 @@ __device__ __forceinline__ double sum_partials_re<double>(const double* p, int n
 }
 int vec_blocks(int64_t n12, int nslices, bool slice_blocks) {
     int nb = (int)((n12 + 4 * kBlock - 1) / (4 * kBlock));
-    // slice_blocks (update kernel of the basis forms): at most 256 vector
+    // slice_blocks (update kernel): at most 256 vector
     // blocks per source, each block reducing the stencil partials once for
     // more of the vector (at 16^4 x 4 the update took 3.33 / 5.75 ms per
     // step in FP64 / FP32 with 256, 3.46 / 5.95 with 512, 3.36 / 6.28 with
     // 1024, and more with 128 or 192), plus one block per 256-shift slice,
     // which advances the slice while the others share the vector pass.
-    // Otherwise up to 512 blocks, every one also taking vector work.
+    // Otherwise (one-off vector kernels) up to 512 blocks.
     if (slice_blocks) return (nb > 256 ? 256 : nb) + nslices;
     if (nb > 512) nb = 512;
     return nb < nslices ? nslices : nb;
@@ -295,16 +297,13 @@ __device__ __forceinline__ SeedScalars seed_scalars(const JobDesc& J, int n, dou
 }
 
 // The seed iteration's second kernel (after the stencil), for every form:
-// scalars, shift bookkeeping (the 256-shift slice of block bx), then one pass
-// over the components: r_{k+1} = r_k - alpha q (basis forms; two-pass second
-// pass also s += h_{k+1} r_{k+1}), or that with the shift sweep (fused:
-// s += c_j alpha^j p_j; reference: x_j += alpha^j p_j; then
-// p_j = r_{k+1}/pi_{k+1} + beta^j p_j).  In the first iteration p_j = b for
-// every j, read from b instead.  The seed direction p is never formed: the
+// scalars, shift bookkeeping (the 256-shift slice of block bx < nslices; the
+// sweep forms also record the chunk's sweep coefficients), then one pass over
+// the components by the other blocks: r_{k+1} = r_k - alpha q (two-pass second
+// pass also s += h_{k+1} r_{k+1}).  The seed direction p is never formed: the
 // stencil builds q_{k+1} = A r_{k+1} + beta_k q_k from r_{k+1} directly.
-template <typename R, int KIND>  // KIND 0 basis / two-pass, 1 fused sweep, 2 reference sweep
+template <typename R>
 __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, int k) {
-    constexpr bool SWEEP = KIND != 0;
     const int f = sizeof(R) == 4 ? 1 : 0;
     const ShiftDev& sh = J.sh;
     SrcState& S = J.st[n];
@@ -334,88 +333,59 @@ __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, in
             sd[2] = make_double2(sc.rr, sc.rrn);
         }
     }
-    const double2 c1 = cdiv(cmul(sc.alpha, S.beta[(k + 1) & 1]), S.alpha[(k + 1) & 1]);
-    const size_t stride3 = (size_t)sh.nsrc * sh.J;
-    // LDS list of the active shifts (sweep forms)
-    extern __shared__ unsigned char lds_raw[];
-    double2* l_coef = reinterpret_cast<double2*>(lds_raw);
-    double2* l_ipi = l_coef + sh.J;
-    double2* l_b = l_ipi + sh.J;
-    int* l_j = reinterpret_cast<int*>(l_b + sh.J);
-    __shared__ int wcount[kBlock / 64];
-    __shared__ int base;
-    if (SWEEP) {
-        if (threadIdx.x == 0) base = 0;
-        __syncthreads();
-    }
-    for (int j0 = 0; j0 < sh.J; j0 += kBlock) {
-        const bool mine = (j0 / kBlock) == bx;  // this block keeps the state of slice j0
-        if (!SWEEP && !mine) continue;
-        const int j = j0 + threadIdx.x;
+    if (bx < sh.nslices) {
+        // the blocks that advance a shift slice take no part in the vector
+        // pass, so the slice bookkeeping runs beside it
+        const double2 c1 = cdiv(cmul(sc.alpha, S.beta[(k + 1) & 1]), S.alpha[(k + 1) & 1]);
+        const size_t stride3 = (size_t)sh.nsrc * sh.J;
+        const int j = bx * kBlock + threadIdx.x;
         const size_t o = (size_t)n * sh.J + j;
         const bool act = j < sh.J && sh.active[(size_t)(k & 1) * stride3 + o] != 0;
         ShiftScalars t{};
         if (act) t = shift_scalars(sh, o, j, k, sc, c1, S.bb);
-        if (mine) {
-            int stay = 0;
-            if (j < sh.J) {
-                if (act) {
-                    sh.pi[(size_t)((k + 1) % 3) * stride3 + o] = t.pn;
-                    sh.aj[o] = t.aj;
-                    sh.res[o] = t.res;
-                    stay = (t.res > sh.tol && isfinite(t.res)) ? 1 : 0;
-                }
-                sh.active[(size_t)((k + 1) & 1) * stride3 + o] = stay;
-                if (sh.h_a != nullptr) {
-                    const size_t ho = ((size_t)n * (sh.maxk + 1) + k) * sh.J + j;
-                    sh.h_a[ho] = act ? t.aj : make_double2(0, 0);
-                    sh.h_b[ho] = act ? t.bj : make_double2(0, 0);
-                    sh.h_pi[ho + sh.J] = act ? t.pn : make_double2(1, 0);
-                }
-            }
-            double tot = (double)stay, mx = act ? t.res : 0.0;  // (shm: 2 kBlock/64 values)
-            block_sum_max<kBlock>(tot, mx, shm);
-            if (threadIdx.x == 0) {
-                cnt_next[bx] = (int)(tot + 0.5);
-                sh.mres[(size_t)n * kMaxSlices + bx] = mx;
-            }
-        }
-        if (SWEEP) {
-            const double2 coef = act ? (KIND == 2 ? t.aj : cmul(sh.c[j], t.aj)) : make_double2(0, 0);
-            const unsigned long long m = __ballot(act);
-            const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-            const int before = __popcll(m & ((1ull << lane) - 1ull));
-            if (lane == 0) wcount[w] = __popcll(m);
-            __syncthreads();
-            int off = base;
-            for (int i = 0; i < w; ++i) off += wcount[i];
+        int stay = 0;
+        if (j < sh.J) {
             if (act) {
-                l_j[off + before] = j;
-                l_coef[off + before] = coef;
-                l_ipi[off + before] = t.ipi;
-                l_b[off + before] = t.bj;
+                sh.pi[(size_t)((k + 1) % 3) * stride3 + o] = t.pn;
+                sh.aj[o] = t.aj;
+                sh.res[o] = t.res;
+                stay = (t.res > sh.tol && isfinite(t.res)) ? 1 : 0;
             }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                int tot = 0;
-                for (int i = 0; i < kBlock / 64; ++i) tot += wcount[i];
-                base += tot;
+            sh.active[(size_t)((k + 1) & 1) * stride3 + o] = stay;
+            if (sh.h_a != nullptr) {
+                const size_t ho = ((size_t)n * (sh.maxk + 1) + k) * sh.J + j;
+                sh.h_a[ho] = act ? t.aj : make_double2(0, 0);
+                sh.h_b[ho] = act ? t.bj : make_double2(0, 0);
+                sh.h_pi[ho + sh.J] = act ? t.pn : make_double2(1, 0);
             }
-            __syncthreads();
+            if (J.swc != nullptr) {
+                const int i = k % kSweep;
+                if (act) {
+                    double2* w = J.swc + (o * kSweep + i) * 3;
+                    w[0] = J.form == OVL_FORM_REFERENCE ? t.aj : cmul(sh.c[j], t.aj);
+                    w[1] = t.ipi;
+                    w[2] = t.bj;
+                    J.swn[o] = i + 1;
+                } else if (i == 0) {
+                    J.swn[o] = 0;
+                }
+            }
         }
+        double tot = (double)stay, mx = act ? t.res : 0.0;  // (shm: 2 kBlock/64 values)
+        block_sum_max<kBlock>(tot, mx, shm);
+        if (threadIdx.x == 0) {
+            cnt_next[bx] = (int)(tot + 0.5);
+            sh.mres[(size_t)n * kMaxSlices + bx] = mx;
+        }
+        return;
     }
     const int64_t n12 = 12 * J.g.Vt;
     const R ar = (R)sc.alpha.x, ai = (R)sc.alpha.y;
-    // basis forms: the blocks that advance a shift slice (bx < nslices) take
-    // no part in the vector pass, which the other nbe - nslices blocks share,
-    // so the slice bookkeeping runs beside it instead of before a share of it
-    const int64_t vbx = SWEEP ? bx : bx - sh.nslices;
-    const int64_t vnb = SWEEP ? J.nbe : J.nbe - sh.nslices;
-    if (vbx < 0) return;
+    const int64_t vbx = bx - sh.nslices, vnb = J.nbe - sh.nslices;
     const C2<R>* ri = job_rk<const C2<R>>(J, k, f) + (size_t)n * n12;
     C2<R>* ro = job_rk<C2<R>>(J, k + 1, f) + (size_t)n * n12;
     const C2<R>* qq = static_cast<const C2<R>*>(J.q[f]) + (size_t)n * n12;
-    if constexpr (!SWEEP && sizeof(R) == 4) {
+    if constexpr (sizeof(R) == 4) {
         // FP32: two components per lane in one 16-byte access of each array
         // (every vector starts 16-byte aligned and 12 Vt is even)
         const bool acc2 = J.h != nullptr;
@@ -445,7 +415,7 @@ __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, in
                 sacc[2 * e + 1] = s1;
             }
         }
-    } else if constexpr (!SWEEP) {
+    } else {
         const bool acc2 = J.h != nullptr;
         const double2 hk = acc2 ? J.h[(size_t)n * (sh.maxk + 1) + k + 1] : make_double2(0, 0);
         double2* sacc = J.s64 + (size_t)n * n12;
@@ -460,51 +430,13 @@ __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, in
                 sacc[e] = sv;
             }
         }
-    } else {
-        const int nl = base;
-        C2<R>* pj = static_cast<C2<R>*>(J.pj[f]);
-        double2* acc_out = KIND == 2 ? J.xj : J.s64;
-        const double2* b0 = J.b64;
-        for (int64_t e = (int64_t)bx * kBlock + threadIdx.x; e < n12; e += (int64_t)J.nbe * kBlock) {
-            const cx<R> r = ld<R>(ri, e), qv = ld<R>(qq, e);
-            const cx<R> rv = mk<R>(r.re - (ar * qv.re - ai * qv.im), r.im - (ar * qv.im + ai * qv.re));
-            stc<R>(ro, e, rv);
-            const cx<R> bfirst = (k == 0) ? mk<R>((R)b0[(size_t)n * n12 + e].x, (R)b0[(size_t)n * n12 + e].y)
-                                          : mk<R>(0, 0);
-            double sre = 0.0, sim = 0.0;
-            for (int l = 0; l < nl; ++l) {
-                const int j = l_j[l];
-                const double2 ca = l_coef[l], ip = l_ipi[l], bj = l_b[l];
-                C2<R>* pjp = pj + ((size_t)n * sh.J + j) * n12;
-                const cx<R> pv = (k == 0) ? bfirst : ld<R>(pjp, e);
-                if constexpr (KIND == 2) {
-                    double2* xp = acc_out + ((size_t)n * sh.J + j) * n12;
-                    double2 x = xp[e];
-                    x.x += ca.x * (double)pv.re - ca.y * (double)pv.im;
-                    x.y += ca.x * (double)pv.im + ca.y * (double)pv.re;
-                    xp[e] = x;
-                } else {
-                    sre += ca.x * (double)pv.re - ca.y * (double)pv.im;
-                    sim += ca.x * (double)pv.im + ca.y * (double)pv.re;
-                }
-                const R ipr = (R)ip.x, ipi_ = (R)ip.y, bjr = (R)bj.x, bji = (R)bj.y;
-                stc<R>(pjp, e, mk<R>(rv.re * ipr - rv.im * ipi_ + bjr * pv.re - bji * pv.im,
-                                     rv.re * ipi_ + rv.im * ipr + bjr * pv.im + bji * pv.re));
-            }
-            if constexpr (KIND == 1) {
-                double2 sv = acc_out[(size_t)n * n12 + e];
-                sv.x += sre;
-                sv.y += sim;
-                acc_out[(size_t)n * n12 + e] = sv;
-            }
-        }
     }
 }
 
 // The iteration counter lives in two device slots: iteration k reads slot
 // kread and the update kernel's first lane publishes k + 1 in the other slot,
 // kwrite, which no block of the same launch reads.
-template <typename R, int KIND>
+template <typename R>
 __global__ __launch_bounds__(kBlock) void k_update_jobs(const JobDesc* __restrict__ jobs, int njobs,
                                                         const int* __restrict__ kread,
                                                         int* __restrict__ kwrite) {
@@ -514,33 +446,174 @@ __global__ __launch_bounds__(kBlock) void k_update_jobs(const JobDesc* __restric
     if (blockIdx.x == 0 && threadIdx.x == 0) *kwrite = k + 1;
     const VecBlock v = vec_block(jobs, njobs);
     if (jobs[v.j].phase != (sizeof(R) == 4 ? 1 : 0)) return;  // the other precision's job
-    update_block<R, KIND>(jobs[v.j], v.n, v.bx, k);
+    update_block<R>(jobs[v.j], v.n, v.bx, k);
 }
 
 template <typename R>
 void launch_iteration_update(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
-                             int vec_blocks_total, int form, int maxJ, hipStream_t s,
-                             hipEvent_t ev0, hipEvent_t ev1) {
+                             int vec_blocks_total, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const dim3 grid(vec_blocks_total), blk(kBlock);
-    const size_t lds = (size_t)maxJ * (3 * sizeof(double2) + sizeof(int));
-    auto go = [&](auto kern, size_t shmem) {
-        if (ev0)
-            hipExtLaunchKernelGGL(kern, grid, blk, (uint32_t)shmem, s, ev0, ev1, 0, jobs, njobs,
-                                  kread, kwrite);
-        else
-            hipLaunchKernelGGL(kern, grid, blk, shmem, s, jobs, njobs, kread, kwrite);
-    };
-    if (form == OVL_FORM_BASIS || form == OVL_FORM_TWOPASS)
-        go(k_update_jobs<R, 0>, 0);
-    else if (form == OVL_FORM_FUSED)
-        go(k_update_jobs<R, 1>, lds);
+    if (ev0)
+        hipExtLaunchKernelGGL(k_update_jobs<R>, grid, blk, 0, s, ev0, ev1, 0, jobs, njobs, kread,
+                              kwrite);
     else
-        go(k_update_jobs<R, 2>, lds);
+        hipLaunchKernelGGL(k_update_jobs<R>, grid, blk, 0, s, jobs, njobs, kread, kwrite);
 }
-template void launch_iteration_update<double>(const JobDesc*, int, const int*, int*, int, int, int,
+template void launch_iteration_update<double>(const JobDesc*, int, const int*, int*, int,
                                               hipStream_t, hipEvent_t, hipEvent_t);
-template void launch_iteration_update<float>(const JobDesc*, int, const int*, int*, int, int, int,
+template void launch_iteration_update<float>(const JobDesc*, int, const int*, int*, int,
                                              hipStream_t, hipEvent_t, hipEvent_t);
+
+// The shift sweep of the last kSweep iterations k0 .. k0 + kSweep - 1, for
+// every shift j active in some of them, from the residuals r_{k0+1} ..
+// (still in their ring of kSweep buffers) and the coefficients the update
+// kernel recorded (swc[.][i] = (coefficient, 1/pi_{k+1}^j, beta^j) of
+// iteration k = k0 + i, swn = the iterations shift j took part in):
+//   fused:     s += c_j alpha^j p_j,   reference: x_j += alpha^j p_j;   then
+//   p_j = r_{k+1}/pi_{k+1} + beta^j p_j
+// applied in iteration order to the value held in registers.  In the first
+// iteration p_j = b for every j, read from b instead.
+// Bound: reading and writing every active p_j (and x_j) once per sweep, and
+// 12 FP64 multiply-adds per element, shift and iteration; a sweep inside every
+// iteration's update moved 16 times the bytes (12^4, 2 sources, 2 x 64 nodes:
+// sgn(H_W) b 48.9 ms, 41.3 ms of it in the update; with this kernel 15.4 ms).
+// A block takes 64 elements, its four waves every fourth active shift, so a
+// lattice of a few hundred sites still spreads; their sums meet in LDS in wave
+// order.
+template <typename R, bool REF>
+__global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict__ jobs,
+                                                       const int* __restrict__ kdev) {
+    constexpr int NW = kBlock / 64;
+    const JobDesc& J = jobs[blockIdx.y];
+    constexpr int f = sizeof(R) == 4 ? 1 : 0;
+    if (J.phase != f) return;  // the other precision's job
+    const int64_t n12 = 12 * J.g.Vt;
+    const int per = (int)(n12 / 64);
+    const int n = (int)blockIdx.x / per;
+    if (n >= J.nsrc) return;
+    const int k0 = (int)uniform((uint32_t)*kdev) - kSweep;
+    if (J.st[n].iter <= k0) return;  // finished before this chunk
+    const ShiftDev& sh = J.sh;
+    const int lane = (int)(threadIdx.x & 63), w = (int)uniform(threadIdx.x >> 6);
+    // the shifts active in the chunk, in order
+    __shared__ int l_j[kMaxSweepShifts], l_n[kMaxSweepShifts];
+    __shared__ int wcount[NW];
+    int nl = 0;
+    for (int j0 = 0; j0 < sh.J; j0 += kBlock) {
+        const int j = j0 + (int)threadIdx.x;
+        const int c = j < sh.J ? J.swn[(size_t)n * sh.J + j] : 0;
+        const unsigned long long m = __ballot(c > 0);
+        if (lane == 0) wcount[w] = __popcll(m);
+        __syncthreads();
+        int off = nl, tot = 0;
+        for (int i = 0; i < NW; ++i) {
+            if (i < w) off += wcount[i];
+            tot += wcount[i];
+        }
+        if (c > 0) {
+            const int at = off + __popcll(m & ((1ull << lane) - 1ull));
+            l_j[at] = j;
+            l_n[at] = c;
+        }
+        nl += tot;
+        __syncthreads();
+    }
+    const int64_t e = (int64_t)((int)blockIdx.x % per) * 64 + lane;
+    const int64_t ve = (int64_t)n * n12 + e;
+    const C2<R>* rbase = static_cast<const C2<R>*>(J.r[f]);
+    const int64_t rpp = (int64_t)J.rpp;
+    cx<R> r[kSweep];
+#pragma unroll
+    for (int i = 0; i < kSweep; ++i)  // (k0 is a multiple of kSweep)
+        r[i] = ld<R>(rbase, (int64_t)((1 + i) % kSweep) * rpp + ve);
+    const bool first = k0 == 0;
+    cx<R> b0 = mk<R>(0, 0);
+    if (first) {
+        const cx<double> b = ld<double>(J.b64, ve);
+        b0 = mk<R>((R)b.re, (R)b.im);
+    }
+    C2<R>* pj = static_cast<C2<R>*>(J.pj[f]);
+    double sre = 0.0, sim = 0.0;
+    // (constant address space: the coefficients are the same for the whole
+    // wave and come through scalar loads)
+    typedef const __attribute__((address_space(4))) double* Cst;
+    const int step = NW;
+    int l = w;
+    cx<R> pnext = b0;
+    if (l < nl && !first)
+        pnext = ld<R>(pj, ((int64_t)n * sh.J + (int)uniform((uint32_t)l_j[l])) * n12 + e);
+    for (; l < nl; l += step) {
+        const int j = (int)uniform((uint32_t)l_j[l]), cnt = (int)uniform((uint32_t)l_n[l]);
+        const int64_t o = ((int64_t)n * sh.J + j) * n12 + e;
+        cx<R> p = pnext;
+        if (l + step < nl && !first)  // the next shift's direction, in flight meanwhile
+            pnext = ld<R>(pj, ((int64_t)n * sh.J + (int)uniform((uint32_t)l_j[l + step])) * n12 + e);
+        const Cst cf = (Cst)(const double*)(J.swc + ((size_t)n * sh.J + j) * kSweep * 3);
+        cx<double> x = mk<double>(0, 0);
+        if constexpr (REF) x = ld<double>(J.xj, o);
+        double tre = 0.0, tim = 0.0;
+        auto step_of = [&](int i) {
+            const double cr = cf[6 * i], ci = cf[6 * i + 1];
+            const R ir = (R)cf[6 * i + 2], ii = (R)cf[6 * i + 3];
+            const R br = (R)cf[6 * i + 4], bi = (R)cf[6 * i + 5];
+            tre += cr * (double)p.re - ci * (double)p.im;
+            tim += cr * (double)p.im + ci * (double)p.re;
+            p = mk<R>(r[i].re * ir - r[i].im * ii + br * p.re - bi * p.im,
+                      r[i].re * ii + r[i].im * ir + br * p.im + bi * p.re);
+        };
+        // four iterations at a time, their scalar loads together; a shift
+        // that stopped within the four takes them one by one
+#pragma unroll
+        for (int g = 0; g < kSweep; g += 4) {
+            if (cnt >= g + 4) {
+#pragma unroll
+                for (int i = g; i < g + 4; ++i) step_of(i);
+            } else if (cnt > g) {
+#pragma unroll
+                for (int i = g; i < g + 3; ++i)
+                    if (cnt > i) step_of(i);
+            }
+        }
+        stc<R>(pj, o, p);
+        if constexpr (REF) {
+            stc<double>(J.xj, o, mk<double>(x.re + tre, x.im + tim));
+        } else {
+            sre += tre;
+            sim += tim;
+        }
+    }
+    if constexpr (!REF) {
+        __shared__ double2 part[NW][64];
+        part[w][lane] = make_double2(sre, sim);
+        __syncthreads();
+        if (w == 0) {
+            cx<double> sv = ld<double>(J.s64, ve);
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                sv.re += part[i][lane].x;
+                sv.im += part[i][lane].y;
+            }
+            stc<double>(J.s64, ve, sv);
+        }
+    }
+}
+
+int sweep_units(int64_t n12, int nsrc) { return (int)(n12 / 64) * nsrc; }
+template <typename R>
+void launch_sweep_jobs(const JobDesc* jobs, int njobs, const int* kdev, int units, int form,
+                       hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    const dim3 grid((unsigned)units, (unsigned)njobs), blk(kBlock);
+    auto go = [&](auto kern) {
+        if (ev0) hipExtLaunchKernelGGL(kern, grid, blk, 0, s, ev0, ev1, 0, jobs, kdev);
+        else hipLaunchKernelGGL(kern, grid, blk, 0, s, jobs, kdev);
+    };
+    if (form == OVL_FORM_REFERENCE) go(k_sweep_jobs<R, true>);
+    else go(k_sweep_jobs<R, false>);
+}
+template void launch_sweep_jobs<double>(const JobDesc*, int, const int*, int, int, hipStream_t,
+                                        hipEvent_t, hipEvent_t);
+template void launch_sweep_jobs<float>(const JobDesc*, int, const int*, int, int, hipStream_t,
+                                       hipEvent_t, hipEvent_t);
 
 // two-pass form, second pass: s = h_0 b (r_0 = b)
 __global__ __launch_bounds__(kBlock) void k_s_init(const double2* __restrict__ b,

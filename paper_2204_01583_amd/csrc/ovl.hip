@@ -114,7 +114,8 @@ struct ovl_ctx {
     DBuf b64, r64, p64, q64, r32, q32, s64, pj64, pj32, xj;
     std::vector<DBuf> slot_chunks;   // basis forms: kSlotChunk residual slots each
     size_t slot_chunk_bytes = 0;
-    DBuf part_w, part_b, state, shifts, lists, nodes_dev, hist, W, h, seed;
+    DBuf part_w, part_b, state, shifts, nodes_dev, hist, W, h, seed;
+    DBuf sweep;  // sweep forms: the chunk's sweep coefficients and active counts
     // iterations per rhs and maxk of the last solve, whose seed scalars stay in
     // `seed` until the next one (for ovl_spectral_bounds)
     std::vector<int> last_iters;
@@ -352,7 +353,7 @@ extern "C" int ovl_destroy(ovl_ctx* ctx) {
     DBuf* bufs[] = {&ctx->U64,  &ctx->U32, &ctx->U64c, &ctx->U32c,   &ctx->hw_in,  &ctx->hw_out, &ctx->b64,   &ctx->r64,
                     &ctx->p64,  &ctx->q64,   &ctx->r32,    &ctx->q32,   &ctx->s64,
                     &ctx->pj64, &ctx->pj32,  &ctx->xj,     &ctx->part_w, &ctx->part_b,
-                    &ctx->state, &ctx->shifts, &ctx->lists, &ctx->nodes_dev, &ctx->hist, &ctx->W,
+                    &ctx->state, &ctx->shifts, &ctx->sweep, &ctx->nodes_dev, &ctx->hist, &ctx->W,
                     &ctx->h,    &ctx->seed,    &ctx->bench_a, &ctx->bench_b, &ctx->bench_c, &ctx->tune_state, &ctx->tune_flush, &ctx->chk, &ctx->fY, &ctx->fX, &ctx->fpsi,
                     &ctx->facc, &ctx->fc, &ctx->fpart, &ctx->slot_table, &ctx->jobs_dev};
     for (DBuf* b : bufs) b->release();
@@ -1046,7 +1047,10 @@ struct Work {
     int k_switch;          // first basis slot (or iteration) held in FP32 (mixed), or -1
     int k_conv;            // iteration before which the job was converted to FP32, or -1
     int K;                 // seed iterations of the last solve (max over sources)
-    size_t rpp;            // two-pass: elements between the two r buffers
+    size_t rpp;            // elements between two r buffers (two-pass: 2, sweep forms: kSweep)
+    int rmask;             // number of r buffers - 1
+    double2* swc;          // sweep forms: coefficients and counts of the chunk (JobDesc)
+    int* swn;
     char** slot_tab;       // basis: device table of slot-chunk bases
     int n_tab;             // chunks published in slot_tab
     double2 *dz, *cj, *zj;
@@ -1085,11 +1089,14 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w) {
     const size_t vec64 = (size_t)nsrc * N * sizeof(double2);
     const size_t vec32 = (size_t)nsrc * N * sizeof(float2);
     const bool twopass = form == OVL_FORM_TWOPASS;
+    const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
+    // r_k's buffers: r_k and r_{k+1} (two-pass), or every residual of a sweep
+    const size_t nr = twopass ? 2 : sweep ? kSweep : 1;
     w.fused = ctx->fused_iter && (form == OVL_FORM_BASIS || twopass);
     const size_t nq = w.fused ? 2 : 1;  // q buffers
     w.qpp = (size_t)nsrc * N;
     HIPCHK(ctx, ctx->b64.ensure(vec64));
-    HIPCHK(ctx, ctx->r64.ensure(twopass ? 2 * vec64 : vec64));
+    HIPCHK(ctx, ctx->r64.ensure(nr * vec64));
     HIPCHK(ctx, ctx->p64.ensure(vec64));
     HIPCHK(ctx, ctx->q64.ensure(nq * vec64));
     HIPCHK(ctx, ctx->s64.ensure(vec64));
@@ -1103,15 +1110,22 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w) {
     w.chunks.clear();
     w.slot_bytes = vec64;
     w.rpp = (size_t)nsrc * N;
+    w.rmask = (int)nr - 1;
+    w.swc = nullptr;
+    w.swn = nullptr;
     w.slot_tab = nullptr;
     w.n_tab = 0;
     if (mixed) {
-        HIPCHK(ctx, ctx->r32.ensure(twopass ? 2 * vec32 : vec32));
+        HIPCHK(ctx, ctx->r32.ensure(nr * vec32));
         HIPCHK(ctx, ctx->q32.ensure(nq * vec32));
         w.r32 = ctx->r32.as<float2>();
         w.q32 = ctx->q32.as<float2>();
     }
-    if (form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE) {
+    if (sweep) {
+        const size_t nc = (size_t)nsrc * J * kSweep * 3;
+        HIPCHK(ctx, ctx->sweep.ensure(nc * sizeof(double2) + (size_t)nsrc * J * sizeof(int)));
+        w.swc = ctx->sweep.as<double2>();
+        w.swn = reinterpret_cast<int*>(w.swc + nc);
         HIPCHK(ctx, ctx->pj64.ensure(vec64 * J));
         w.pj64 = ctx->pj64.as<double2>();
         if (mixed) {
@@ -1137,7 +1151,7 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w) {
     }
     const int nslices = (J + 255) / 256;
     w.nbw = wilson_blocks(ctx->g);
-    w.nbe = vec_blocks(N, nslices, basis || twopass);
+    w.nbe = vec_blocks(N, nslices, true);
     HIPCHK(ctx, ctx->part_w.ensure(nq * (size_t)nsrc * w.nbw * sizeof(double4)));
     // ||b||^2 partials of the initialisation: one per block of its own grid
     // (launch_init_state), which is not the update kernel's
@@ -1270,6 +1284,7 @@ bool graphs_enabled(const ovl_ctx* ctx) {
 }
 
 constexpr int kChunk = 16;  // seed iterations per captured graph / per convergence poll
+static_assert(kChunk == kSweep, "one shift sweep per chunk");
 // iteration i of a chunk reads the counter slot i & 1, so a chunk starts at slot 0
 static_assert(kChunk % 2 == 0, "chunks must hold an even number of iterations");
 
@@ -1278,7 +1293,7 @@ struct Batch {
     std::vector<Work*> w;
     std::vector<JobDesc> desc;
     int sten_total[2] = {0, 0};  // stencil grid of the FP64 and of the FP32 variant
-    int vec_total = 0, variant64 = 0, variant32 = 0, form = 0, maxJ = 0;
+    int vec_total = 0, variant64 = 0, variant32 = 0, form = 0, sweep_units = 0;
     int lnk[2] = {0, 0};  // link format of the FP64 and of the FP32 stencil
     bool fused = false;   // one-kernel iteration: variant64/32 are fused-kernel variants
     int check_variant = 0, check_lnk = 0;  // H_W stencil of the in-band check
@@ -1313,6 +1328,9 @@ void fill_desc(ovl_ctx* c, Work& w, JobDesc& d, const int (&variant)[2], const i
     d.q[0] = w.q64; d.q[1] = w.q32;
     d.r[0] = w.r64; d.r[1] = w.r32;
     d.rpp = w.rpp;
+    d.rmask = w.rmask;
+    d.swc = w.swc;
+    d.swn = w.swn;
     d.b64 = w.b64;
     d.s64 = w.s64;
     d.pj[0] = w.pj64; d.pj[1] = w.pj32;
@@ -1342,20 +1360,19 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
                    int nact_total) {
     ovl_ctx* lead = B.ctx[0];
     const bool sweep = B.form == OVL_FORM_FUSED || B.form == OVL_FORM_REFERENCE;
-    double vec_b[2] = {0, 0}, sweep_b[2] = {0, 0};
-    if (prof) {
+    double sweep_b[2] = {0, 0};
+    if (prof && sweep) {
+        // the residuals of the chunk and s read once, s written; p_j of the active
+        // shifts read and written (and x_j in the reference form)
+        const bool ref = B.form == OVL_FORM_REFERENCE;
         for (size_t i = 0; i < B.w.size(); ++i) {
             const int f = B.desc[i].phase;
             const double es = f ? sizeof(float2) : sizeof(double2);
-            const double V = (double)B.ctx[i]->g.V, n = B.w[i]->nsrc, N = 12 * V;
-            vec_b[f] += 3.0 * es * N * n;  // r and q read, r written
-            const bool ref = B.form == OVL_FORM_REFERENCE;
-            sweep_b[f] += N * n * (ref ? 0.0 : 32.0);  // s read and written (fused sweep)
+            sweep_b[f] += 12.0 * (double)B.ctx[i]->g.V * B.w[i]->nsrc * (kSweep * es + (ref ? 0.0 : 32.0));
         }
         const int f0 = B.desc[0].phase;
         const double es0 = f0 ? sizeof(float2) : sizeof(double2);
-        const double N0 = 12.0 * B.ctx[0]->g.V;
-        sweep_b[f0] += N0 * nact_total * (2.0 * es0 + (B.form == OVL_FORM_REFERENCE ? 32.0 : 0.0));
+        sweep_b[f0] += 12.0 * (double)B.ctx[0]->g.V * nact_total * (2.0 * es0 + (ref ? 32.0 : 0.0));
     }
     const int vars[2] = {B.variant64, B.variant32};
     const int nj = (int)B.desc.size();
@@ -1385,14 +1402,22 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
         }
         for (int f = 0; f < 2; ++f) {
             if (!(mode & (1 << f))) continue;
-            // K2: r update (r, q read, r written), with the sweep in the sweep forms
-            ProfScope ps(lead, s, prof ? (sweep ? 4 + f : 2 + f) : -1,
-                         sweep ? vec_b[f] + sweep_b[f] : 0.0, true);
-            if (f) launch_iteration_update<float>(B.desc_dev, nj, kr, kw, B.vec_total, B.form,
-                                                  B.maxJ, s, ps.start(), ps.stop());
-            else launch_iteration_update<double>(B.desc_dev, nj, kr, kw, B.vec_total, B.form,
-                                                 B.maxJ, s, ps.start(), ps.stop());
+            // K2: r update (r, q read, r written)
+            ProfScope ps(lead, s, prof ? 2 + f : -1, 0.0, true);
+            if (f) launch_iteration_update<float>(B.desc_dev, nj, kr, kw, B.vec_total, s,
+                                                  ps.start(), ps.stop());
+            else launch_iteration_update<double>(B.desc_dev, nj, kr, kw, B.vec_total, s,
+                                                 ps.start(), ps.stop());
         }
+    }
+    for (int f = 0; f < 2 && sweep; ++f) {
+        if (!(mode & (1 << f))) continue;
+        int* kd = B.kdev + (count & 1);
+        ProfScope ps(lead, s, prof ? 4 + f : -1, sweep_b[f], true);
+        if (f) launch_sweep_jobs<float>(B.desc_dev, nj, kd, B.sweep_units, B.form, s, ps.start(),
+                                        ps.stop());
+        else launch_sweep_jobs<double>(B.desc_dev, nj, kd, B.sweep_units, B.form, s, ps.start(),
+                                       ps.stop());
     }
     // the chunk's final state to the pinned host slots (the counter after an
     // even number of iterations is in slot 0)
@@ -1407,7 +1432,7 @@ int replay_chunk(Batch& B, int mode, hipStream_t s) {
     char kb[256];
     snprintf(kb, sizeof(kb), "%p|%p|%zu|%d|%d|%d|%d|%d|%d|%d|%d|%d|%d", (void*)B.desc_dev,
              (void*)B.kdev, B.desc.size(), B.sten_total[0], B.sten_total[1], B.vec_total,
-             B.variant64, B.variant32, B.form, B.maxJ, B.lnk[0], B.lnk[1], (int)B.fused);
+             B.variant64, B.variant32, B.form, B.sweep_units, B.lnk[0], B.lnk[1], (int)B.fused);
     auto& gc = lead->graphs[mode - 1];
     if (!gc.exec || gc.key != kb) {
         if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
@@ -1480,11 +1505,10 @@ void convert_job(ovl_ctx* c, Work& w, int k, hipStream_t s) {
         launch_convert_64_to_32(slot_ptr<double2>(w, k), w.r32, n, s);
         (void)hipMemcpyAsync(slot_ptr<float2>(w, k), w.r32, (size_t)n * sizeof(float2),
                              hipMemcpyDeviceToDevice, s);
-    } else if (c->form == OVL_FORM_TWOPASS) {
-        launch_convert_64_to_32(w.r64 + (size_t)(k & 1) * w.rpp, w.r32 + (size_t)(k & 1) * w.rpp, n, s);
     } else {
-        launch_convert_64_to_32(w.r64, w.r32, n, s);
-        launch_convert_64_to_32(w.pj64, w.pj32, n * w.J, s);
+        const size_t at = (size_t)(k & w.rmask) * w.rpp;
+        launch_convert_64_to_32(w.r64 + at, w.r32 + at, n, s);
+        if (c->form != OVL_FORM_TWOPASS) launch_convert_64_to_32(w.pj64, w.pj32, n * w.J, s);
     }
 }
 
@@ -1567,7 +1591,6 @@ PollResult read_state(Batch& B, int slot, int k_host, hipEvent_t ev, int* rc_out
 void credit_live_bytes(const Batch& B) {
     ovl_ctx* lead = B.ctx[0];
     if (!lead->prof_on) return;
-    const bool sweep = B.form == OVL_FORM_FUSED || B.form == OVL_FORM_REFERENCE;
     for (size_t i = 0; i < B.w.size(); ++i) {
         const ovl_ctx* c = B.ctx[i];
         const Work& w = *B.w[i];
@@ -1607,7 +1630,7 @@ void credit_live_bytes(const Batch& B) {
                 mx = std::max(mx, itf);
             }
             lead->prof_bytes[0 + f] += V * es * (36.0 * sum + (B.lnk[f] ? 24.0 : 36.0) * mx);
-            if (!sweep) lead->prof_bytes[2 + f] += 3.0 * 12.0 * V * es * sum;
+            lead->prof_bytes[2 + f] += 3.0 * 12.0 * V * es * sum;
         }
     }
 }
@@ -1639,13 +1662,13 @@ static void layout_grids(Batch& B, const std::vector<char>& retired) {
 // precision phase `phase`, and uploads it.
 static int build_desc(Batch& B, hipStream_t s, int phase = 0) {
     ovl_ctx* lead = B.ctx[0];
-    B.maxJ = 0;
+    B.sweep_units = 0;
     B.desc.resize(B.w.size());
     int sb[2] = {0, 0}, vb = 0;
     const int vars[2] = {B.variant64, B.variant32};
     for (size_t i = 0; i < B.w.size(); ++i) {
         fill_desc(B.ctx[i], *B.w[i], B.desc[i], vars, B.lnk, sb, vb);
-        B.maxJ = std::max(B.maxJ, B.w[i]->J);
+        B.sweep_units = std::max(B.sweep_units, sweep_units(B.w[i]->N, B.w[i]->nsrc));
         // the chunk kernels export the state into the pinned slots
         JobDesc& d = B.desc[i];
         void* hdev = nullptr;

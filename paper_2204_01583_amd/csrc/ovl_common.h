@@ -157,6 +157,7 @@ struct ShiftDev {
 // one launch advances every job of a batch by one stage.
 constexpr int kMaxJobs = 64;
 constexpr int kSlotChunk = 32;  // basis form: residual slots per allocation
+constexpr int kSweep = 16;      // sweep forms: seed iterations per shift sweep
 // Grid blocks a job owns in a job-table stencil launch: its block count
 // padded to a multiple of 8 (one per XCD), so every job starts on XCD 0.
 inline __host__ __device__ int job_grid_blocks(int nb) { return (nb + 7) & ~7; }
@@ -180,12 +181,16 @@ struct JobDesc {
     size_t qpp;                 // fused iteration: elements between q[k&1 = 0] and q[1]
     // working vectors [nsrc][12 Vt], index [0] FP64, [1] FP32
     void* q[2];
-    void* r[2];                 // fused/reference: r in place; two-pass: r_k at r[..] + (k&1) * rpp
-    size_t rpp;                 // two-pass: element offset of the second r buffer
+    void* r[2];                 // all but the basis form: r_k at r[..] + (k & rmask) * rpp
+    size_t rpp;                 // elements between two r buffers
+    int rmask;                  // two-pass: 1 (two buffers); sweep forms: kSweep - 1
     double2* b64;               // packed source
     double2* s64;               // quadrature sum
     void* pj[2];                // sweep forms: [nsrc][J][12 Vt]
     double2* xj;                // reference form
+    double2* swc;               // sweep forms: [nsrc][J][kSweep][3] coefficients of the chunk's
+                                // iterations (see k_sweep_jobs)
+    int* swn;                   // sweep forms: [nsrc][J] iterations of the chunk shift j was active in
     char* const* slots;         // basis form: device table of slot-chunk bases
     size_t slot_bytes;          // bytes of one slot (nsrc * 12 Vt FP64 complex)
     const double2* h;           // two-pass, second pass: h[src][i] weights of r_i
@@ -208,8 +213,7 @@ __device__ __forceinline__ T* job_rk(const JobDesc& J, int k, int fp32) {
     if (J.form == 2) {  // basis: slot k (FP32 slots packed at the slot base)
         return reinterpret_cast<T*>(J.slots[k / kSlotChunk] + (size_t)(k % kSlotChunk) * J.slot_bytes);
     }
-    T* r = static_cast<T*>(J.r[fp32]);
-    return J.form == 3 ? r + (size_t)(k & 1) * J.rpp : r;
+    return static_cast<T*>(J.r[fp32]) + (size_t)(k & J.rmask) * J.rpp;
 }
 
 }  // namespace ovl

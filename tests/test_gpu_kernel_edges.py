@@ -2,11 +2,13 @@
 remainders, the smallest and largest of a range."""
 import functools
 
+import numpy as np
 import pytest
 
 import seeded_inputs as si
 from oracle.contour import nodes
 from oracle.force import force as oracle_force
+from oracle.wilson import hermitian_wilson
 from tests.gpu_util import CIRCLE, assert_close, gauge, make_ctx, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +45,47 @@ def test_rebuilt_solutions_at_tile_edges(precision, fused, tol, chunk, monkeypat
     assert abs(S - S_ref) / S_ref < (1e-11 if precision == 0 else 1e-8)
     assert_close(G.cpu().numpy(), G_ref, tol, f"G p{precision} fused {fused} chunk {chunk}")
     ctx.close()
+
+
+@functools.lru_cache(maxsize=None)
+def _dense(dims):
+    return hermitian_wilson(gauge(dims, 0.3, 6), 1.4).toarray()
+
+
+# The shift sweep: shift counts around a block's four waves, the 64 lanes of
+# one and the 256 of a block, padding sites (90 sites), two sources, both sweep
+# forms, FP64 and mixed; tolerances of the sign tests at these precisions.
+@pytest.mark.parametrize("precision,tol", [(0, 1e-11), (1, 1e-10)])
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("n", [1, 3, 5, 64, 65, 257])
+def test_sweep_shift_counts(form, n, precision, tol):
+    dims = (3, 5, 2, 3)
+    z, c = nodes(258, *CIRCLE)
+    z, c = z[::2][:n], c[::2][:n]
+    b = si.gaussian_sources(dims, 2, first_seed=41)
+    H = _dense(dims)
+    lam, Q = np.linalg.eigh(H)
+    f = (c[:, None] / (z[:, None] - lam[None, :])).sum(0)
+    ref = np.stack([Q @ (f * (Q.conj().T @ v.ravel())) for v in b]).reshape(b.shape)
+    ctx = make_ctx(dims, gauge(dims, 0.3, 6), precision=precision, form=form, tol=1e-12)
+    ctx.set_nodes(z, c)
+    s, st = ctx.apply_sign(to_dev(b))
+    assert_close(s.cpu().numpy(), ref, tol, f"form {form}, {n} shifts, {st.iterations} iterations")
+    ctx.close()
+
+
+# Iteration limits that end inside a sweep: the last iterate equals the stored
+# basis form's, which sums the same iterations in another order.
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("maxiter", [1, 15, 16, 17, 31])
+def test_sweep_ends_inside_a_chunk(form, maxiter):
+    dims = (3, 5, 2, 3)
+    b = to_dev(si.gaussian_sources(dims, 2, first_seed=43))
+    out = {}
+    for fm in (form, 2):
+        ctx = make_ctx(dims, gauge(dims, 0.3, 6), nq=16, form=fm, tol=1e-12, maxiter=maxiter)
+        s, st = ctx.apply_sign(b, allow_not_converged=True)
+        assert st.iterations == maxiter and st.n_active_end > 0
+        out[fm] = s.cpu().numpy()
+        ctx.close()
+    assert_close(out[form], out[2], 1e-12, f"form {form}, {maxiter} iterations")
