@@ -90,7 +90,7 @@ typedef struct {
     double  seconds;           /* wall time of the apply on the stream                       */
     int32_t stencil_variant64; /* stencil choice used in FP64 (autotuned; see ovl_bench_kernel);
                                   1000 + v + 8 f for the fused iteration's variant v and link
-                                  format f (basis forms)                                    */
+                                  format f, 2000 + f for the split iteration (basis forms)   */
     int32_t stencil_variant32; /* ... in FP32, or -1                                        */
     double  max_true_rel_res;  /* max ||b - (z_j - H) x_j|| / ||b|| over the checked shifts, or
                                   -1 when not checked (see ovl_set_residual_check)           */
@@ -289,11 +289,14 @@ int ovl_get_stats(const ovl_ctx* ctx, ovl_stats* st);
  * OVL_AUTOTUNE_VERBOSE=1 prints every candidate's time to stderr.  The basis
  * forms time their stencil inside the solve (a chunk of a real solve from
  * its initial state, discarded; the four fastest choices are timed twice
- * more and each keeps its fastest run).  OVL_FUSED=1, read when a context is created, makes
- * the basis forms run one fused kernel per seed
- * iteration instead of the stencil and update kernels (slower on MI355X;
- * kept as a parity-tested alternative), with OVL_ITER_VARIANT=v forcing its
- * variant v < 8.
+ * more and each keeps its fastest run).  Solves of at most 36864 sites x
+ * sources (over the whole batch) run one kernel per seed iteration with one
+ * hop per lane instead and tune nothing, unless OVL_STENCIL_VARIANT is set.
+ * OVL_FUSED, read when a context is created: 0 keeps the stencil and update
+ * kernels at every size; 1 makes the basis forms run one fused kernel per
+ * seed iteration with one lane per site (slower on MI355X; kept as a
+ * parity-tested alternative), with OVL_ITER_VARIANT=v forcing its variant
+ * v < 8.
  * Buffers are internal scratch (contents arbitrary but finite). */
 int ovl_bench_kernel(ovl_ctx* ctx, int32_t which, int32_t nrhs, int32_t reps,
                      double* avg_ms, double* bytes);

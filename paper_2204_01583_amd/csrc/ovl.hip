@@ -101,9 +101,10 @@ struct ovl_ctx {
     double2 zseed = make_double2(1.0, 0.05);
     double switch_res = 1e-4;
     int poll = 8;  // iterations between convergence polls
-    // OVL_FUSED=1: the basis forms run the fused one-kernel iteration instead
-    // of the two-kernel one (stencil, then update)
-    bool fused_iter = false;
+    // OVL_FUSED: 1 the basis forms run the fused one-kernel iteration instead of
+    // the two-kernel one (stencil, then update), 0 never; unset (-1), small
+    // problems run the split one-kernel iteration (split_iteration)
+    int fused_iter = -1;
     void* scratch = nullptr;  // this device's address of the ovl_apply_hw_noalloc scratch
     // device buffers
     DBuf U64, U32;    // links, tiled [mu][Vt/64][9][64], boundary sign folded in
@@ -338,7 +339,7 @@ extern "C" int ovl_create(ovl_ctx** out, const int32_t dims[4], const int32_t bc
         ctx->scratch = scratch_address(device);
     }
     const char* fz = getenv("OVL_FUSED");
-    ctx->fused_iter = fz && fz[0] == '1';
+    ctx->fused_iter = fz && *fz ? (fz[0] == '1') : -1;
     *out = ctx;
     return OVL_OK;
 }
@@ -1043,6 +1044,7 @@ struct Work {
     ShiftDev sh;
     int var64, var32;      // stencil variants (autotuned)
     bool fused;            // one-kernel iteration (basis forms): q and the partials double-buffered
+    bool split;            // ... in its one-hop-per-lane kernel
     size_t qpp;            // fused: elements between q[0] and q[1]
     int k_switch;          // first basis slot (or iteration) held in FP32 (mixed), or -1
     int k_conv;            // iteration before which the job was converted to FP32, or -1
@@ -1074,7 +1076,22 @@ const char* host_slot(const ovl_ctx* c, const Work& w, int slot) {
     return reinterpret_cast<const char*>(c->host_state) + (size_t)slot * state_slot_bytes(w);
 }
 
-int prepare(ovl_ctx* ctx, int nsrc, Work& w) {
+// Whether the basis forms run the split one-kernel iteration (split.hip):
+// where the whole solve has at most kSplitSites sites x sources, unless a
+// kernel is asked for by name.  Its one launch per iteration beats the two
+// kernels' latency, its doubled neighbour loads lose to their bytes; per
+// iteration, two kernels / split, in us (FP64, FP32): 4096 sites 20.1 / 10.9,
+// 19.7 / 10.5; 16384 21.7 / 14.2, 20.7 / 13.5; 32768 24.9 / 23.1, 22.5 / 19.7;
+// 40960 27.6 / 27.8, 23.5 / 24.7; 65536 33.2 / 45.7, 26.4 / 38.2.
+constexpr int64_t kSplitSites = 36864;
+bool split_iteration(const ovl_ctx* ctx, int64_t sites) {
+    const char* force = getenv("OVL_STENCIL_VARIANT");
+    return ctx->fused_iter < 0 && !(force && *force) && sites <= kSplitSites;
+}
+
+// Work buffers of a solve on ctx with nsrc sources; sites: the site x sources
+// of the whole (possibly batched) solve.
+int prepare(ovl_ctx* ctx, int nsrc, Work& w, int64_t sites) {
     const int J = (int)ctx->z.size();
     const int64_t N = n12(ctx);
     const bool mixed = ctx->precision == OVL_PREC_MIXED;
@@ -1092,7 +1109,8 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w) {
     const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
     // r_k's buffers: r_k and r_{k+1} (two-pass), or every residual of a sweep
     const size_t nr = twopass ? 2 : sweep ? kSweep : 1;
-    w.fused = ctx->fused_iter && (form == OVL_FORM_BASIS || twopass);
+    w.split = (form == OVL_FORM_BASIS || twopass) && split_iteration(ctx, sites);
+    w.fused = w.split || (ctx->fused_iter == 1 && (form == OVL_FORM_BASIS || twopass));
     const size_t nq = w.fused ? 2 : 1;  // q buffers
     w.qpp = (size_t)nsrc * N;
     HIPCHK(ctx, ctx->b64.ensure(vec64));
@@ -1150,7 +1168,7 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w) {
         ctx->slot_chunk_bytes = vec64 * kSlotChunk;
     }
     const int nslices = (J + 255) / 256;
-    w.nbw = wilson_blocks(ctx->g);
+    w.nbw = w.split ? split_tiles(ctx->g) : wilson_blocks(ctx->g);
     w.nbe = vec_blocks(N, nslices, true);
     HIPCHK(ctx, ctx->part_w.ensure(nq * (size_t)nsrc * w.nbw * sizeof(double4)));
     // ||b||^2 partials of the initialisation: one per block of its own grid
@@ -1296,6 +1314,7 @@ struct Batch {
     int vec_total = 0, variant64 = 0, variant32 = 0, form = 0, sweep_units = 0;
     int lnk[2] = {0, 0};  // link format of the FP64 and of the FP32 stencil
     bool fused = false;   // one-kernel iteration: variant64/32 are fused-kernel variants
+    bool split = false;   // ... in its one-hop-per-lane kernel, which has one variant
     int check_variant = 0, check_lnk = 0;  // H_W stencil of the in-band check
     JobDesc* desc_dev = nullptr;
     int* kdev = nullptr;
@@ -1310,11 +1329,12 @@ void fill_desc(ovl_ctx* c, Work& w, JobDesc& d, const int (&variant)[2], const i
     d.U[0] = lnk[0] ? c->U64c.p : c->U64.p;
     d.U[1] = lnk[1] ? c->U32c.p : c->U32.p;
     d.nsrc = w.nsrc;
-    d.nsb = wilson_blocks(c->g);
+    d.nsb = w.nbw;
     for (int f = 0; f < 2; ++f) {
         d.sten_b0[f] = sten_b0[f];
-        d.sten_nb[f] = w.fused ? iter_grid_blocks(c->g, w.nsrc)
-                               : wilson_grid_blocks(c->g, w.nsrc, variant[f]);
+        d.sten_nb[f] = w.split   ? split_grid_blocks(c->g, w.nsrc, w.sh.nslices)
+                       : w.fused ? iter_grid_blocks(c->g, w.nsrc)
+                                 : wilson_grid_blocks(c->g, w.nsrc, variant[f]);
         sten_b0[f] += job_grid_blocks(d.sten_nb[f]);
     }
     d.vec_b0 = vec_b0;
@@ -1384,7 +1404,13 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
                 if (!(mode & (1 << f))) continue;
                 // bytes credited after the solve from the sources' live iterations
                 ProfScope ps(lead, s, prof ? 8 + f : -1, 0.0, true);
-                if (f) launch_iter_jobs<float>(B.desc_dev, nj, kr, kw, B.sten_total[1], vars[1],
+                if (B.split && f)
+                    launch_iter_split<float>(B.desc_dev, nj, kr, kw, B.sten_total[1], B.lnk[1], s,
+                                             ps.start(), ps.stop());
+                else if (B.split)
+                    launch_iter_split<double>(B.desc_dev, nj, kr, kw, B.sten_total[0], B.lnk[0], s,
+                                              ps.start(), ps.stop());
+                else if (f) launch_iter_jobs<float>(B.desc_dev, nj, kr, kw, B.sten_total[1], vars[1],
                                                B.lnk[1], s, ps.start(), ps.stop());
                 else launch_iter_jobs<double>(B.desc_dev, nj, kr, kw, B.sten_total[0], vars[0],
                                               B.lnk[0], s, ps.start(), ps.stop());
@@ -1432,7 +1458,8 @@ int replay_chunk(Batch& B, int mode, hipStream_t s) {
     char kb[256];
     snprintf(kb, sizeof(kb), "%p|%p|%zu|%d|%d|%d|%d|%d|%d|%d|%d|%d|%d", (void*)B.desc_dev,
              (void*)B.kdev, B.desc.size(), B.sten_total[0], B.sten_total[1], B.vec_total,
-             B.variant64, B.variant32, B.form, B.sweep_units, B.lnk[0], B.lnk[1], (int)B.fused);
+             B.variant64, B.variant32, B.form, B.sweep_units, B.lnk[0], B.lnk[1],
+             (int)B.fused + (int)B.split);
     auto& gc = lead->graphs[mode - 1];
     if (!gc.exec || gc.key != kb) {
         if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
@@ -1820,9 +1847,17 @@ static int solve_batch_once(Batch& B) {
     bool all12 = true;
     for (ovl_ctx* c : B.ctx) all12 = all12 && c->links12;
     B.fused = B.w[0]->fused;
+    B.split = B.w[0]->split;
     for (Work* w : B.w)
-        if (w->fused != B.fused) return fail(lead, OVL_E_ARG, "mixed iteration kinds in one batch");
-    if (B.fused) {
+        if (w->fused != B.fused || w->split != B.split)
+            return fail(lead, OVL_E_ARG, "mixed iteration kinds in one batch");
+    if (B.split) {
+        // its only variant, with the two-row links where they are allowed; the
+        // in-band check's one H_W with two hops per step and the LDS tile
+        B.variant64 = B.variant32 = 0;
+        B.lnk[0] = B.lnk[1] = all12 ? 1 : 0;
+        B.check_variant = 17;
+    } else if (B.fused) {
         // fused iteration: its own variants (hops per step, block order, LDS tile)
         const int c64 = iter_variant(B.ctx[big], B.w[big]->nsrc, 0);
         const int c32 = mixed ? iter_variant(B.ctx[big], B.w[big]->nsrc, 1) : 0;
@@ -2125,7 +2160,10 @@ static int solve_batch_once(Batch& B) {
         L.n_active_end = na;
         L.max_est_rel_res = mr;
         L.seconds = ms * 1e-3;
-        if (B.fused) {
+        if (B.split) {
+            L.stencil_variant64 = 2000 + B.lnk[0];
+            L.stencil_variant32 = mixed ? 2000 + B.lnk[1] : -1;
+        } else if (B.fused) {
             L.stencil_variant64 = 1000 + B.variant64 + kIterVariants * B.lnk[0];
             L.stencil_variant32 = mixed ? 1000 + B.variant32 + kIterVariants * B.lnk[1] : -1;
         } else {
@@ -2465,7 +2503,7 @@ static int apply_common(ovl_ctx* ctx, const void* in, void* out, int nrhs, ovl_s
     int rc = check_apply_args(ctx, in, out, nrhs, true);
     if (rc) return rc;
     Work w;
-    rc = prepare(ctx, nrhs, w);
+    rc = prepare(ctx, nrhs, w, ctx->g.V * nrhs);
     if (rc) return rc;
     launch_pack_spinor64(static_cast<const double2*>(in), w.b64, ctx->g.V, ctx->g.Vt, nrhs, ctx->stream);
     HIPCHK(ctx, hipGetLastError());
@@ -2552,7 +2590,7 @@ extern "C" int ovl_force(ovl_ctx* ctx, const void* phi, void* grad, int32_t kind
     //    kept implicit in the stored basis and coefficients
     ctx->form = OVL_FORM_BASIS;
     Work w;
-    rc = prepare(ctx, 1, w);
+    rc = prepare(ctx, 1, w, ctx->g.V);
     if (rc) { restore(); return rc; }
     launch_pack_spinor64(static_cast<const double2*>(phi), w.b64, ctx->g.V, ctx->g.Vt, 1, s);
     const int rc1 = solve(ctx, w);
@@ -2591,7 +2629,7 @@ extern "C" int ovl_force(ovl_ctx* ctx, const void* phi, void* grad, int32_t kind
     swap_basis();
     for (int j = 0; j < J; ++j) ctx->z[j].y = -z0[j].y;
     Work w2;
-    rc = prepare(ctx, 1, w2);
+    rc = prepare(ctx, 1, w2, ctx->g.V);
     if (rc) { restore(); return rc; }
     HIPCHK(ctx, hipMemcpyAsync(w2.b64, ctx->fpsi.p, N * sizeof(double2), hipMemcpyDeviceToDevice, s));
     const int rc2 = solve(ctx, w2);
@@ -2678,9 +2716,11 @@ extern "C" int ovl_apply_sign_batched(ovl_ctx* const* ctxs, int32_t nctx, const 
     std::vector<Work> works(nctx);
     Batch B;
     int rc = OVL_OK;
+    int64_t sites = 0;
+    for (int i = 0; i < nctx; ++i) sites += ctxs[i]->g.V * std::max(nrhs[i], 0);
     for (int i = 0; i < nctx && rc == OVL_OK; ++i) {
         rc = check_apply_args(ctxs[i], in[i], out[i], nrhs[i], true);
-        if (rc == OVL_OK) rc = prepare(ctxs[i], nrhs[i], works[i]);
+        if (rc == OVL_OK) rc = prepare(ctxs[i], nrhs[i], works[i], sites);
         if (rc != OVL_OK && ctxs[i] != lead) {
             fail(lead, rc, "context %d: %s", i, ctxs[i]->err);
         }

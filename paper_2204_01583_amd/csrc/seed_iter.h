@@ -17,38 +17,37 @@ struct SeedScalars {
     double rr, rrn;
     int status;
 };
-__device__ __forceinline__ SeedScalars seed_scalars_from(const double4* pw, int nsb, double* shm) {
-    double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    for (int b = threadIdx.x; b < nsb; b += kBlock) {
-        const double4 v = pw[b];
-        a0 += v.x;
-        a1 += v.y;
-        a2 += v.z;
-        a3 += v.w;
-    }
-    double a[4] = {a0, a1, a2, a3};
-    block_sum4<kBlock>(a, shm);  // shm: 4 kBlock/64 values
-    a0 = a[0];
-    a1 = a[1];
-    a2 = a[2];
-    a3 = a[3];
+// from the sums a = (Re <r,q>, Im <r,q>, ||q||^2, ||r||^2)
+__device__ __forceinline__ SeedScalars seed_scalars_of(const double (&a)[4]) {
     SeedScalars r;
-    const double2 rq = make_double2(a0, a1);
-    r.rr = a3;
+    const double2 rq = make_double2(a[0], a[1]);
+    r.rr = a[3];
     r.status = 0;
-    if (!finite2(rq) || !isfinite(a2) || !isfinite(a3)) r.status = OVL_E_NONFINITE;
-    else if (cabs2(rq) <= 1e-300 * a3) r.status = OVL_E_BREAKDOWN;
+    if (!finite2(rq) || !isfinite(a[2]) || !isfinite(a[3])) r.status = OVL_E_NONFINITE;
+    else if (cabs2(rq) <= 1e-300 * a[3]) r.status = OVL_E_BREAKDOWN;
     if (r.status) {
         r.alpha = r.beta = make_double2(0, 0);
         r.rrn = 0;
         return r;
     }
-    r.alpha = cdiv(make_double2(a3, 0.0), rq);
-    r.rrn = fmax(cabs2(r.alpha) * a2 - a3, 0.0);
+    r.alpha = cdiv(make_double2(a[3], 0.0), rq);
+    r.rrn = fmax(cabs2(r.alpha) * a[2] - a[3], 0.0);
     const double2 ph = cdiv(r.alpha, make_double2(r.alpha.x, -r.alpha.y));
-    const double ratio = r.rrn / a3;
+    const double ratio = r.rrn / a[3];
     r.beta = make_double2(ph.x * ratio, ph.y * ratio);
     return r;
+}
+__device__ __forceinline__ SeedScalars seed_scalars_from(const double4* pw, int nsb, double* shm) {
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int b = threadIdx.x; b < nsb; b += kBlock) {
+        const double4 v = pw[b];
+        a[0] += v.x;
+        a[1] += v.y;
+        a[2] += v.z;
+        a[3] += v.w;
+    }
+    block_sum4<kBlock>(a, shm);  // shm: 4 kBlock/64 values
+    return seed_scalars_of(a);
 }
 
 // Per-shift scalars of iteration k for shift j (active at the start of k):
@@ -82,7 +81,9 @@ __device__ __forceinline__ ShiftScalars shift_scalars(const ShiftDev& sh, size_t
 // previous ones in S: pi_{i+1}^j, alpha^j, beta^j, the residual estimate and
 // deactivation, the slice's active count into cnt[(i+1)&1] and its largest
 // estimate, and the basis-form history of row i.  The same arithmetic as the
-// scalar part of the two-kernel update.
+// scalar part of the two-kernel update.  NT: the block's threads, of which the
+// first 256 take a shift.
+template <int NT = kBlock>
 __device__ __forceinline__ void advance_shift_slice(const ShiftDev& sh, const SrcState& S, int n,
                                                     int slice, int i, const SeedScalars& sc,
                                                     double* shm) {
@@ -91,11 +92,12 @@ __device__ __forceinline__ void advance_shift_slice(const ShiftDev& sh, const Sr
     int* cnt_next = sh.cnt + ((size_t)((i + 1) & 1) * sh.nsrc + n) * kMaxSlices;
     const int j = slice * kBlock + threadIdx.x;
     const size_t o = (size_t)n * sh.J + j;
-    const bool act = j < sh.J && sh.active[(size_t)(i & 1) * stride3 + o] != 0;
+    const bool mine = (NT == kBlock || threadIdx.x < kBlock) && j < sh.J;
+    const bool act = mine && sh.active[(size_t)(i & 1) * stride3 + o] != 0;
     ShiftScalars t{};
     if (act) t = shift_scalars(sh, o, j, i, sc, c1, S.bb);
     int stay = 0;
-    if (j < sh.J) {
+    if (mine) {
         if (act) {
             sh.pi[(size_t)((i + 1) % 3) * stride3 + o] = t.pn;
             sh.aj[o] = t.aj;
@@ -110,8 +112,8 @@ __device__ __forceinline__ void advance_shift_slice(const ShiftDev& sh, const Sr
             sh.h_pi[ho + sh.J] = act ? t.pn : make_double2(1, 0);
         }
     }
-    double tot = (double)stay, mx = act ? t.res : 0.0;  // (shm: 2 kBlock/64 values)
-    block_sum_max<kBlock>(tot, mx, shm);
+    double tot = (double)stay, mx = act ? t.res : 0.0;  // (shm: 2 NT/64 values)
+    block_sum_max<NT>(tot, mx, shm);
     if (threadIdx.x == 0) {
         cnt_next[slice] = (int)(tot + 0.5);
         sh.mres[(size_t)n * kMaxSlices + slice] = mx;

@@ -89,3 +89,45 @@ def test_sweep_ends_inside_a_chunk(form, maxiter):
         out[fm] = s.cpu().numpy()
         ctx.close()
     assert_close(out[form], out[2], 1e-12, f"form {form}, {maxiter} iterations")
+
+
+# The split iteration: lattices below, at and above one 64-site tile, shift
+# counts around its 256-shift slices, both link formats, both basis forms.
+@pytest.mark.parametrize("precision,tol", [(0, 1e-11), (1, 1e-10)])
+@pytest.mark.parametrize("form,links", [(2, "two-row"), (2, "full"), (3, "two-row")])
+@pytest.mark.parametrize("dims,n,nsrc", [((2, 2, 2, 2), 2, 1), ((4, 4, 2, 2), 256, 2),
+                                         ((3, 5, 2, 3), 258, 3), ((5, 3, 3, 4), 600, 1)])
+def test_split_iteration(dims, n, nsrc, form, links, precision, tol, monkeypatch):
+    if links == "full":
+        monkeypatch.setenv("OVL_LINKS", "full")
+    z, c = nodes(600, *CIRCLE)
+    z, c = z[::2][:n], c[::2][:n]
+    b = si.gaussian_sources(dims, nsrc, first_seed=47)
+    lam, Q = np.linalg.eigh(_dense(dims))
+    f = (c[:, None] / (z[:, None] - lam[None, :])).sum(0)
+    ref = np.stack([Q @ (f * (Q.conj().T @ v.ravel())) for v in b]).reshape(b.shape)
+    ctx = make_ctx(dims, gauge(dims, 0.3, 6), precision=precision, form=form, tol=1e-12)
+    ctx.set_nodes(z, c)
+    s, st = ctx.apply_sign(to_dev(b))
+    assert st.stencil_variant64 == 2000 + (links == "two-row")
+    assert_close(s.cpu().numpy(), ref, tol, f"{dims} x {nsrc}, form {form}, {n} shifts")
+    ctx.close()
+
+
+# Both sides of the split iteration's size limit: the same result from either
+# iteration.
+@pytest.mark.parametrize("precision,tol", [(0, 1e-11), (1, 1e-10)])
+@pytest.mark.parametrize("dims,nsrc,split", [((16, 16, 8, 18), 1, True), ((16, 17, 8, 17), 1, False),
+                                             ((8, 8, 8, 12), 6, True), ((8, 8, 8, 12), 7, False)])
+def test_split_iteration_limit(dims, nsrc, split, precision, tol, monkeypatch):
+    b = to_dev(si.gaussian_sources(dims, nsrc, first_seed=53))
+    out = []
+    for fused in ("", "0"):
+        monkeypatch.setenv("OVL_FUSED", fused)
+        monkeypatch.setenv("OVL_AUTOTUNE", "0")
+        ctx = make_ctx(dims, gauge(dims, 0.3, 6), nq=16, precision=precision, form=2, tol=1e-12)
+        s, st = ctx.apply_sign(b)
+        assert (st.stencil_variant64 >= 2000) == (split and fused == "")
+        out.append(s.cpu().numpy())
+        ctx.close()
+    assert_close(out[0], out[1], tol, f"{dims} x {nsrc}")
