@@ -90,7 +90,7 @@ typedef struct {
     double  seconds;           /* wall time of the apply on the stream                       */
     int32_t stencil_variant64; /* stencil choice used in FP64 (autotuned; see ovl_bench_kernel);
                                   1000 + v + 8 f for the fused iteration's variant v and link
-                                  format f, 2000 + f for the split iteration (basis forms)   */
+                                  format f (basis forms), 2000 + f for the split iteration   */
     int32_t stencil_variant32; /* ... in FP32, or -1                                        */
     double  max_true_rel_res;  /* max ||b - (z_j - H) x_j|| / ||b|| over the checked shifts, or
                                   -1 when not checked (see ovl_set_residual_check)           */
@@ -293,7 +293,7 @@ int ovl_get_stats(const ovl_ctx* ctx, ovl_stats* st);
  * sources (over the whole batch) run one kernel per seed iteration with one
  * hop per lane instead and tune nothing, unless OVL_STENCIL_VARIANT is set.
  * OVL_FUSED, read when a context is created: 0 keeps the stencil and update
- * kernels at every size; 1 makes the basis forms run one fused kernel per
+ * kernels at every size and form; 1 makes the basis forms run one fused kernel per
  * seed iteration with one lane per site (slower on MI355X; kept as a
  * parity-tested alternative), with OVL_ITER_VARIANT=v forcing its variant
  * v < 8.

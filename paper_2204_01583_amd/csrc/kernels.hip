@@ -336,47 +336,7 @@ __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, in
     if (bx < sh.nslices) {
         // the blocks that advance a shift slice take no part in the vector
         // pass, so the slice bookkeeping runs beside it
-        const double2 c1 = cdiv(cmul(sc.alpha, S.beta[(k + 1) & 1]), S.alpha[(k + 1) & 1]);
-        const size_t stride3 = (size_t)sh.nsrc * sh.J;
-        const int j = bx * kBlock + threadIdx.x;
-        const size_t o = (size_t)n * sh.J + j;
-        const bool act = j < sh.J && sh.active[(size_t)(k & 1) * stride3 + o] != 0;
-        ShiftScalars t{};
-        if (act) t = shift_scalars(sh, o, j, k, sc, c1, S.bb);
-        int stay = 0;
-        if (j < sh.J) {
-            if (act) {
-                sh.pi[(size_t)((k + 1) % 3) * stride3 + o] = t.pn;
-                sh.aj[o] = t.aj;
-                sh.res[o] = t.res;
-                stay = (t.res > sh.tol && isfinite(t.res)) ? 1 : 0;
-            }
-            sh.active[(size_t)((k + 1) & 1) * stride3 + o] = stay;
-            if (sh.h_a != nullptr) {
-                const size_t ho = ((size_t)n * (sh.maxk + 1) + k) * sh.J + j;
-                sh.h_a[ho] = act ? t.aj : make_double2(0, 0);
-                sh.h_b[ho] = act ? t.bj : make_double2(0, 0);
-                sh.h_pi[ho + sh.J] = act ? t.pn : make_double2(1, 0);
-            }
-            if (J.swc != nullptr) {
-                const int i = k % kSweep;
-                if (act) {
-                    double2* w = J.swc + (o * kSweep + i) * 3;
-                    w[0] = J.form == OVL_FORM_REFERENCE ? t.aj : cmul(sh.c[j], t.aj);
-                    w[1] = t.ipi;
-                    w[2] = t.bj;
-                    J.swn[o] = i + 1;
-                } else if (i == 0) {
-                    J.swn[o] = 0;
-                }
-            }
-        }
-        double tot = (double)stay, mx = act ? t.res : 0.0;  // (shm: 2 kBlock/64 values)
-        block_sum_max<kBlock>(tot, mx, shm);
-        if (threadIdx.x == 0) {
-            cnt_next[bx] = (int)(tot + 0.5);
-            sh.mres[(size_t)n * kMaxSlices + bx] = mx;
-        }
+        advance_shift_slice(J, S, n, bx, k, sc, shm);
         return;
     }
     const int64_t n12 = 12 * J.g.Vt;
@@ -464,10 +424,12 @@ template void launch_iteration_update<double>(const JobDesc*, int, const int*, i
 template void launch_iteration_update<float>(const JobDesc*, int, const int*, int*, int,
                                              hipStream_t, hipEvent_t, hipEvent_t);
 
-// The shift sweep of the last kSweep iterations k0 .. k0 + kSweep - 1, for
-// every shift j active in some of them, from the residuals r_{k0+1} ..
-// (still in their ring of kSweep buffers) and the coefficients the update
-// kernel recorded (swc[.][i] = (coefficient, 1/pi_{k+1}^j, beta^j) of
+// The shift sweep of the last kSweep iterations k0 .. k0 + kSweep - 1 whose
+// shifts have been advanced (in the one-kernel iteration the chunk's last
+// kernel has advanced them by the iteration before its own, lag = 1, so the
+// first window starts at -1), for every shift j active in some of them, from
+// the residuals r_{k0+1} ..  (still in their ring of kSweep buffers) and the
+// recorded coefficients (swc[.][i] = (coefficient, 1/pi_{k+1}^j, beta^j) of
 // iteration k = k0 + i, swn = the iterations shift j took part in):
 //   fused:     s += c_j alpha^j p_j,   reference: x_j += alpha^j p_j;   then
 //   p_j = r_{k+1}/pi_{k+1} + beta^j p_j
@@ -491,8 +453,9 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
     const int per = (int)(n12 / 64);
     const int n = (int)blockIdx.x / per;
     if (n >= J.nsrc) return;
-    const int k0 = (int)uniform((uint32_t)*kdev) - kSweep;
-    if (J.st[n].iter <= k0) return;  // finished before this chunk
+    const int lag = J.lag;
+    const int k0 = (int)uniform((uint32_t)*kdev) - kSweep - lag;
+    if (J.st[n].iter <= (k0 > 0 ? k0 : 0)) return;  // finished before this window
     const ShiftDev& sh = J.sh;
     const int lane = (int)(threadIdx.x & 63), w = (int)uniform(threadIdx.x >> 6);
     // the shifts active in the chunk, in order
@@ -524,9 +487,9 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
     const int64_t rpp = (int64_t)J.rpp;
     cx<R> r[kSweep];
 #pragma unroll
-    for (int i = 0; i < kSweep; ++i)  // (k0 is a multiple of kSweep)
-        r[i] = ld<R>(rbase, (int64_t)((1 + i) % kSweep) * rpp + ve);
-    const bool first = k0 == 0;
+    for (int i = 0; i < kSweep; ++i)  // (k0 + lag is a multiple of kSweep)
+        r[i] = ld<R>(rbase, (int64_t)((1 + i - lag) & (kSweep - 1)) * rpp + ve);
+    const bool first = k0 <= 0;
     cx<R> b0 = mk<R>(0, 0);
     if (first) {
         const cx<double> b = ld<double>(J.b64, ve);

@@ -1043,7 +1043,7 @@ struct Work {
     size_t state_bytes;
     ShiftDev sh;
     int var64, var32;      // stencil variants (autotuned)
-    bool fused;            // one-kernel iteration (basis forms): q and the partials double-buffered
+    bool fused;            // one-kernel iteration: q and the partials double-buffered
     bool split;            // ... in its one-hop-per-lane kernel
     size_t qpp;            // fused: elements between q[0] and q[1]
     int k_switch;          // first basis slot (or iteration) held in FP32 (mixed), or -1
@@ -1076,7 +1076,7 @@ const char* host_slot(const ovl_ctx* c, const Work& w, int slot) {
     return reinterpret_cast<const char*>(c->host_state) + (size_t)slot * state_slot_bytes(w);
 }
 
-// Whether the basis forms run the split one-kernel iteration (split.hip):
+// Whether a solve runs the split one-kernel iteration (split.hip):
 // where the whole solve has at most kSplitSites sites x sources, unless a
 // kernel is asked for by name.  Its one launch per iteration beats the two
 // kernels' latency, its doubled neighbour loads lose to their bytes; per
@@ -1109,7 +1109,7 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w, int64_t sites) {
     const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
     // r_k's buffers: r_k and r_{k+1} (two-pass), or every residual of a sweep
     const size_t nr = twopass ? 2 : sweep ? kSweep : 1;
-    w.split = (form == OVL_FORM_BASIS || twopass) && split_iteration(ctx, sites);
+    w.split = split_iteration(ctx, sites);
     w.fused = w.split || (ctx->fused_iter == 1 && (form == OVL_FORM_BASIS || twopass));
     const size_t nq = w.fused ? 2 : 1;  // q buffers
     w.qpp = (size_t)nsrc * N;
@@ -1351,6 +1351,7 @@ void fill_desc(ovl_ctx* c, Work& w, JobDesc& d, const int (&variant)[2], const i
     d.rmask = w.rmask;
     d.swc = w.swc;
     d.swn = w.swn;
+    d.lag = w.fused ? 1 : 0;
     d.b64 = w.b64;
     d.s64 = w.s64;
     d.pj[0] = w.pj64; d.pj[1] = w.pj32;
@@ -1521,8 +1522,9 @@ void convert_job(ovl_ctx* c, Work& w, int k, hipStream_t s) {
             (void)hipMemcpyAsync(slot_ptr<float2>(w, km), w.r32, (size_t)n * sizeof(float2),
                                  hipMemcpyDeviceToDevice, s);
         } else {
-            launch_convert_64_to_32(w.r64 + (size_t)(km & 1) * w.rpp, w.r32 + (size_t)(km & 1) * w.rpp,
-                                    n, s);
+            const size_t at = (size_t)(km & w.rmask) * w.rpp;
+            launch_convert_64_to_32(w.r64 + at, w.r32 + at, n, s);
+            if (c->form != OVL_FORM_TWOPASS) launch_convert_64_to_32(w.pj64, w.pj32, n * w.J, s);
         }
         return;
     }

@@ -191,6 +191,8 @@ struct JobDesc {
     double2* swc;               // sweep forms: [nsrc][J][kSweep][3] coefficients of the chunk's
                                 // iterations (see k_sweep_jobs)
     int* swn;                   // sweep forms: [nsrc][J] iterations of the chunk shift j was active in
+    int lag;                    // 1 in the one-kernel iterations, whose kernel k advances the shifts
+                                // by iteration k - 1; else 0
     char* const* slots;         // basis form: device table of slot-chunk bases
     size_t slot_bytes;          // bytes of one slot (nsrc * 12 Vt FP64 complex)
     const double2* h;           // two-pass, second pass: h[src][i] weights of r_i

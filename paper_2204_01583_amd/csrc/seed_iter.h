@@ -80,13 +80,14 @@ __device__ __forceinline__ ShiftScalars shift_scalars(const ShiftDev& sh, size_t
 // n (one lane per shift), given the seed scalars sc of iteration i and the
 // previous ones in S: pi_{i+1}^j, alpha^j, beta^j, the residual estimate and
 // deactivation, the slice's active count into cnt[(i+1)&1] and its largest
-// estimate, and the basis-form history of row i.  The same arithmetic as the
-// scalar part of the two-kernel update.  NT: the block's threads, of which the
-// first 256 take a shift.
+// estimate, the basis-form history of row i and the sweep forms'
+// coefficients of the iteration.  NT: the block's threads, of which the first
+// 256 take a shift.
 template <int NT = kBlock>
-__device__ __forceinline__ void advance_shift_slice(const ShiftDev& sh, const SrcState& S, int n,
+__device__ __forceinline__ void advance_shift_slice(const JobDesc& J, const SrcState& S, int n,
                                                     int slice, int i, const SeedScalars& sc,
                                                     double* shm) {
+    const ShiftDev& sh = J.sh;
     const double2 c1 = cdiv(cmul(sc.alpha, S.beta[(i + 1) & 1]), S.alpha[(i + 1) & 1]);
     const size_t stride3 = (size_t)sh.nsrc * sh.J;
     int* cnt_next = sh.cnt + ((size_t)((i + 1) & 1) * sh.nsrc + n) * kMaxSlices;
@@ -110,6 +111,18 @@ __device__ __forceinline__ void advance_shift_slice(const ShiftDev& sh, const Sr
             sh.h_a[ho] = act ? t.aj : make_double2(0, 0);
             sh.h_b[ho] = act ? t.bj : make_double2(0, 0);
             sh.h_pi[ho + sh.J] = act ? t.pn : make_double2(1, 0);
+        }
+        if (J.swc != nullptr) {
+            const int at = (i + J.lag) % kSweep;
+            if (act) {
+                double2* w = J.swc + (o * kSweep + at) * 3;
+                w[0] = J.form == OVL_FORM_REFERENCE ? t.aj : cmul(sh.c[j], t.aj);
+                w[1] = t.ipi;
+                w[2] = t.bj;
+                J.swn[o] = at + 1;
+            } else if (at == 0) {
+                J.swn[o] = 0;
+            }
         }
     }
     double tot = (double)stay, mx = act ? t.res : 0.0;  // (shm: 2 NT/64 values)

@@ -91,7 +91,19 @@ __device__ __forceinline__ void iter_split_block(const JobDesc& J, int k, unsign
             if (k <= sh.maxk && threadIdx.x == 0) *cnt_next = 0;
             return;
         }
-        if (k == 0) return;
+        if (k == 0) {
+            // sweep forms: the first sweep's window starts one iteration before
+            // the first, which leaves every p_j as it is
+            const int j = b * kBlock + (int)threadIdx.x;
+            if (J.swc != nullptr && threadIdx.x < kBlock && j < sh.J) {
+                const size_t o = (size_t)n * sh.J + j;
+                double2* c = J.swc + o * kSweep * 3;
+                c[0] = c[1] = make_double2(0, 0);
+                c[2] = make_double2(1, 0);
+                J.swn[o] = 1;
+            }
+            return;
+        }
         const SeedScalars sc = scalars();
         if (sc.status) {
             if (threadIdx.x == 0) {
@@ -112,7 +124,7 @@ __device__ __forceinline__ void iter_split_block(const JobDesc& J, int k, unsign
                 sd[2] = make_double2(sc.rr, sc.rrn);
             }
         }
-        advance_shift_slice<NT>(sh, S, n, b, k - 1, sc, shm);
+        advance_shift_slice<NT>(J, S, n, b, k - 1, sc, shm);
         return;
     }
     if (!live) return;

@@ -810,7 +810,7 @@ __device__ __forceinline__ void iter_block(const JobDesc& J, int k, unsigned til
             sd[2] = make_double2(sc.rr, sc.rrn);
         }
     }
-    for (int q = sb; q < sh.nslices; q += nsb) advance_shift_slice(sh, S, n, q, k - 1, sc, shm);
+    for (int q = sb; q < sh.nslices; q += nsb) advance_shift_slice(J, S, n, q, k - 1, sc, shm);
 }
 
 template <typename R, int HPI, int ORD, int TIL, int LNK>
