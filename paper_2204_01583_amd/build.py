@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libovl.so")
-SOURCES = ["kernels.hip", "stencil.hip", "split.hip", "ovl.hip"]
+SOURCES = ["kernels.hip", "stencil.hip", "split.hip", "hw.hip", "ovl.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

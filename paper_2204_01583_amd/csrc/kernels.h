@@ -52,6 +52,9 @@ void launch_wilson(int mode, const C2<R>* in, C2<R>* out, const C2<R>* U, const 
                    const SrcState* stt, const ShiftDev* sh, int k, int nrhs, hipStream_t s,
                    int variant, int lnk);
 int wilson_blocks(const Geom& g);
+// out = H_W in on the caller's layout [n][V][12], in one launch (hw.hip)
+void launch_hw(const double2* in, double2* out, const double2* U, const Geom& g, double kappa,
+               int nrhs, int lnk, hipStream_t s);
 
 // ---- seed iteration over a job table (device-side iteration counter kdev) --
 // Blocks per source of the vector kernels (see kernels.hip).

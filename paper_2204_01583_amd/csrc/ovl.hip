@@ -19,37 +19,11 @@
 
 using namespace ovl;
 
-// Scratch of ovl_apply_hw_noalloc: the packed input and output spinors of one
-// call.  One copy per GPU, held until the process ends.  In host code the
-// name is a host-side stand-in, not a device address: kernels and copies
-// use the per-device address from hipGetSymbolAddress (scratch_address).
-constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
+// The largest request ovl_apply_hw_noalloc takes, in bytes of its input and
+// output.
+constexpr size_t kNoAllocBytes = (size_t)64 << 20;
 
 namespace {
-
-// Device address of `scratch` on each device, looked up once per device with
-// that device current (ovl_create); null until then or if the lookup failed.
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-void* g_scratch_ptr[kMaxDevices] = {nullptr};
-bool g_scratch_done[kMaxDevices] = {false};
-
-void* scratch_address(int device) {
-    if (device < 0 || device >= kMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    if (!g_scratch_done[device]) {
-        void* ptr = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-        if (e == hipSuccess) {
-            g_scratch_ptr[device] = ptr;
-            g_scratch_done[device] = true;
-        } else {
-            (void)hipGetLastError();
-        }
-    }
-    return g_scratch_ptr[device];
-}
 
 // A device allocation that only grows.  New memory is zeroed before ensure
 // returns, so the padding sites of the tiled layouts start at zero; every
@@ -105,7 +79,6 @@ struct ovl_ctx {
     // the two-kernel one (stencil, then update), 0 never; unset (-1), small
     // problems run the split one-kernel iteration (split_iteration)
     int fused_iter = -1;
-    void* scratch = nullptr;  // this device's address of the ovl_apply_hw_noalloc scratch
     // device buffers
     DBuf U64, U32;    // links, tiled [mu][Vt/64][9][64], boundary sign folded in
     DBuf U64c, U32c;  // rows 0 and 1 only, [mu][Vt/64][6][64] (SU(3) fields)
@@ -332,12 +305,6 @@ extern "C" int ovl_create(ovl_ctx** out, const int32_t dims[4], const int32_t bc
     }
     ctx->g.V = V;
     ctx->g.Vt = (V + kTile - 1) / kTile * kTile;
-    {
-        // the no-allocation entry point's scratch on this device (set-up, with
-        // the device current; a failed lookup only disables that entry point)
-        DeviceGuard dg(device);
-        ctx->scratch = scratch_address(device);
-    }
     const char* fz = getenv("OVL_FUSED");
     ctx->fused_iter = fz && *fz ? (fz[0] == '1') : -1;
     *out = ctx;
@@ -951,11 +918,30 @@ static int check_apply_args(ovl_ctx* ctx, const void* in, const void* out, int n
     return OVL_OK;
 }
 
+// OVL_STENCIL_VARIANT asks for one of the tiled stencil's variants, which H_W
+// alone then goes through (pack, stencil, unpack)
+static bool stencil_forced() {
+    const char* force = getenv("OVL_STENCIL_VARIANT");
+    return force && *force;
+}
+
+// H_W in one launch on the caller's vectors; allocates nothing
+static void apply_hw_direct(ovl_ctx* ctx, const void* in, void* out, int nrhs) {
+    const int lnk = ctx->links12 ? 1 : 0;
+    launch_hw(static_cast<const double2*>(in), static_cast<double2*>(out),
+              stencil_links<double>(ctx, lnk), ctx->g, kappa_of(ctx->m0), nrhs, lnk, ctx->stream);
+}
+
 extern "C" int ovl_apply_hw(ovl_ctx* ctx, const void* in, void* out, int32_t nrhs) {
     if (!ctx) return OVL_E_ARG;
     DeviceGuard dg(ctx->device);
     int rc = check_apply_args(ctx, in, out, nrhs, false);
     if (rc) return rc;
+    if (!stencil_forced()) {
+        apply_hw_direct(ctx, in, out, nrhs);
+        HIPCHK(ctx, hipGetLastError());
+        return OVL_OK;
+    }
     const size_t nb = (size_t)nrhs * n12(ctx) * sizeof(double2);
     HIPCHK(ctx, ctx->hw_in.ensure(nb));
     HIPCHK(ctx, ctx->hw_out.ensure(nb));
@@ -978,25 +964,12 @@ extern "C" int ovl_apply_hw_noalloc(ovl_ctx* ctx, const void* in, void* out, int
     DeviceGuard dg(ctx->device);
     int rc = check_apply_args(ctx, in, out, nrhs, false);
     if (rc) return rc;
-    if (!ctx->scratch) return fail(ctx, OVL_E_HIP, "the static scratch of this device is unavailable");
     const size_t nb = (size_t)nrhs * n12(ctx) * sizeof(double2);
-    if (2 * nb > kNoAllocScratchBytes)
+    if (2 * nb > kNoAllocBytes)
         return fail(ctx, OVL_E_ARG,
-                    "nrhs %d needs %zu bytes of scratch; ovl_apply_hw_noalloc holds %zu "
-                    "(2 nrhs * 12 * Vt complex128)", nrhs, 2 * nb, kNoAllocScratchBytes);
-    // the stencil choice already tuned for this nrhs (by ovl_apply_hw), else
-    // variant 0; never the tuner, which allocates
-    int code = kStencilVariants * (ctx->links12 ? 1 : 0);
-    auto it = ctx->stencil_variant.find(std::make_pair((int)nrhs, 0));
-    if (it != ctx->stencil_variant.end()) code = it->second;
-    const int var = code % kStencilVariants, lnk = code / kStencilVariants;
-    double2* sin = static_cast<double2*>(ctx->scratch);
-    double2* sout = reinterpret_cast<double2*>(static_cast<char*>(ctx->scratch) + nb);
-    launch_pack_spinor64(static_cast<const double2*>(in), sin, ctx->g.V, ctx->g.Vt, nrhs, ctx->stream);
-    launch_wilson<double>(0, sin, sout, stencil_links<double>(ctx, lnk), ctx->g, kappa_of(ctx->m0),
-                          make_double2(0, 0), nullptr, nullptr, nullptr, nullptr, 0, nrhs,
-                          ctx->stream, var, lnk);
-    launch_unpack_spinor64(sout, static_cast<double2*>(out), ctx->g.V, ctx->g.Vt, nrhs, ctx->stream);
+                    "nrhs %d needs %zu bytes (2 nrhs * 12 * Vt complex128); "
+                    "ovl_apply_hw_noalloc takes at most %zu", nrhs, 2 * nb, kNoAllocBytes);
+    apply_hw_direct(ctx, in, out, nrhs);
     HIPCHK(ctx, hipGetLastError());
     return OVL_OK;
 }

@@ -131,3 +131,37 @@ def test_split_iteration_limit(dims, nsrc, split, precision, tol, monkeypatch):
         out.append(s.cpu().numpy())
         ctx.close()
     assert_close(out[0], out[1], tol, f"{dims} x {nsrc}")
+
+
+# H_W on the caller's layout: lattices below, at and beyond one 64-site block,
+# every boundary sign, both link formats; against the oracle's matrix, at the
+# tolerances of the operator tests.
+@pytest.mark.parametrize("links", ["two-row", "full"])
+@pytest.mark.parametrize("dims,nrhs,bc", [((2, 2, 2, 2), 1, (1, 1, 1, -1)),
+                                          ((4, 4, 2, 2), 2, (-1, 1, -1, 1)),
+                                          ((3, 5, 2, 3), 3, (1, -1, 1, -1)),
+                                          ((6, 6, 4, 6), 5, (1, 1, 1, -1))])
+def test_hw_direct_edges(dims, nrhs, bc, links, monkeypatch):
+    if links == "full":
+        monkeypatch.setenv("OVL_LINKS", "full")
+    U = gauge(dims, 0.3, 6)
+    H = hermitian_wilson(U, 1.4, bc=bc)
+    b = si.gaussian_sources(dims, nrhs, first_seed=59)
+    ref = np.stack([(H @ v.ravel()).reshape(v.shape) for v in b])
+    ctx = make_ctx(dims, U, bc=bc)
+    assert_close(ctx.apply_hw(to_dev(b)).cpu().numpy(), ref, 1e-14, f"{dims} FP64 {links}")
+    ctx.close()
+
+
+# Both sides of its rule for the block order (192 MiB of vectors), against the
+# tiled stencil.
+@pytest.mark.parametrize("dims,nrhs", [((16, 16, 16, 16), 16), ((16, 16, 16, 17), 16)])
+def test_hw_direct_matches_the_tiled_stencil(dims, nrhs, monkeypatch):
+    import torch
+    ctx = make_ctx(dims, gauge(dims, 0.3, 6))
+    b = torch.randn((nrhs,) + ctx.site_shape + (4, 3), dtype=torch.complex128, device="cuda")
+    got = ctx.apply_hw(b)
+    monkeypatch.setenv("OVL_STENCIL_VARIANT", "0")
+    ref = ctx.apply_hw(b)
+    assert float((got - ref).abs().max() / ref.abs().max()) < 1e-14
+    ctx.close()
