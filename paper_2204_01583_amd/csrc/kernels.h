@@ -69,6 +69,13 @@ template <typename R>
 void launch_wilson_jobs(const JobDesc* jobs, int njobs, const int* kdev, int total_blocks,
                         int variant, int lnk, hipStream_t s, hipEvent_t ev0 = nullptr,
                         hipEvent_t ev1 = nullptr);
+// The two-pass form's second pass (jobs with J.h set), where the stencil runs
+// variant 16 or 17 (replayable): K1 with the recorded scalars and r_{k+1} in
+// one kernel, which also advances the counter
+inline bool replayable(int variant) { return variant == 16 || variant == 17; }
+template <typename R>
+void launch_wilson_replay(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
+                          int total_blocks, int variant, int lnk, hipStream_t s);
 // K2: seed and shift scalars, shift bookkeeping, r update; reads the iteration
 // index from kread and writes its successor to kwrite
 template <typename R>
@@ -107,6 +114,10 @@ void launch_set_phase(JobDesc* job, int phase, hipStream_t s);
 // read from kdev (the iteration counter after a chunk)
 void launch_export_state(const JobDesc* jobs, int njobs, const int* kdev, int chunk,
                          hipStream_t s);
+// two-pass form, second pass: s += h r over the last kReplay residuals
+template <typename R>
+void launch_replay_sum(const JobDesc* jobs, int njobs, const int* kdev, int vec_blocks_total,
+                       hipStream_t s);
 // two-pass form, second pass: s = h_0 b
 void launch_s_init(const double2* b, const double2* h, int maxk, double2* s, int64_t n12, int nsrc,
                    hipStream_t st);

@@ -299,9 +299,9 @@ __device__ __forceinline__ SeedScalars seed_scalars(const JobDesc& J, int n, dou
 // The seed iteration's second kernel (after the stencil), for every form:
 // scalars, shift bookkeeping (the 256-shift slice of block bx < nslices; the
 // sweep forms also record the chunk's sweep coefficients), then one pass over
-// the components by the other blocks: r_{k+1} = r_k - alpha q (two-pass second
-// pass also s += h_{k+1} r_{k+1}).  The seed direction p is never formed: the
-// stencil builds q_{k+1} = A r_{k+1} + beta_k q_k from r_{k+1} directly.
+// the components by the other blocks: r_{k+1} = r_k - alpha q.  The seed
+// direction p is never formed: the stencil builds q_{k+1} = A r_{k+1} +
+// beta_k q_k from r_{k+1} directly.
 template <typename R>
 __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, int k) {
     const int f = sizeof(R) == 4 ? 1 : 0;
@@ -347,11 +347,8 @@ __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, in
     const C2<R>* qq = static_cast<const C2<R>*>(J.q[f]) + (size_t)n * n12;
     if constexpr (sizeof(R) == 4) {
         // FP32: two components per lane in one 16-byte access of each array
-        // (every vector starts 16-byte aligned and 12 Vt is even)
-        const bool acc2 = J.h != nullptr;
-        const double2 hk = acc2 ? J.h[(size_t)n * (sh.maxk + 1) + k + 1] : make_double2(0, 0);
-        double2* sacc = J.s64 + (size_t)n * n12;
-        // (global address-space pointers: global, not flat, loads and stores)
+        // (every vector starts 16-byte aligned and 12 Vt is even; global
+        // address-space pointers: global, not flat, loads and stores)
         typedef float __attribute__((ext_vector_type(4))) F4;
         const OVL_GLOBAL F4* ri4 = (const OVL_GLOBAL F4*)ri;
         const OVL_GLOBAL F4* qq4 = (const OVL_GLOBAL F4*)qq;
@@ -359,37 +356,13 @@ __device__ __forceinline__ void update_block(const JobDesc& J, int n, int bx, in
         const int64_t n2 = n12 / 2;
         for (int64_t e = vbx * kBlock + threadIdx.x; e < n2; e += vnb * kBlock) {
             const F4 r = ri4[e], qv = qq4[e];
-            F4 rn;
-            rn.x = r.x - ((float)ar * qv.x - (float)ai * qv.y);
-            rn.y = r.y - ((float)ar * qv.y + (float)ai * qv.x);
-            rn.z = r.z - ((float)ar * qv.z - (float)ai * qv.w);
-            rn.w = r.w - ((float)ar * qv.w + (float)ai * qv.z);
-            ro4[e] = rn;
-            if (acc2) {
-                double2 s0 = sacc[2 * e], s1 = sacc[2 * e + 1];
-                s0.x += hk.x * (double)rn.x - hk.y * (double)rn.y;
-                s0.y += hk.x * (double)rn.y + hk.y * (double)rn.x;
-                s1.x += hk.x * (double)rn.z - hk.y * (double)rn.w;
-                s1.y += hk.x * (double)rn.w + hk.y * (double)rn.z;
-                sacc[2 * e] = s0;
-                sacc[2 * e + 1] = s1;
-            }
+            const cx<R> a = sub_scaled<R>(mk<R>(r.x, r.y), ar, ai, mk<R>(qv.x, qv.y));
+            const cx<R> b = sub_scaled<R>(mk<R>(r.z, r.w), ar, ai, mk<R>(qv.z, qv.w));
+            ro4[e] = F4{a.re, a.im, b.re, b.im};
         }
     } else {
-        const bool acc2 = J.h != nullptr;
-        const double2 hk = acc2 ? J.h[(size_t)n * (sh.maxk + 1) + k + 1] : make_double2(0, 0);
-        double2* sacc = J.s64 + (size_t)n * n12;
-        for (int64_t e = vbx * kBlock + threadIdx.x; e < n12; e += vnb * kBlock) {
-            const cx<R> r = ld<R>(ri, e), qv = ld<R>(qq, e);
-            const cx<R> rn = mk<R>(r.re - (ar * qv.re - ai * qv.im), r.im - (ar * qv.im + ai * qv.re));
-            stc<R>(ro, e, rn);
-            if (acc2) {
-                double2 sv = sacc[e];
-                sv.x += hk.x * (double)rn.re - hk.y * (double)rn.im;
-                sv.y += hk.x * (double)rn.im + hk.y * (double)rn.re;
-                sacc[e] = sv;
-            }
-        }
+        for (int64_t e = vbx * kBlock + threadIdx.x; e < n12; e += vnb * kBlock)
+            stc<R>(ro, e, sub_scaled<R>(ld<R>(ri, e), ar, ai, ld<R>(qq, e)));
     }
 }
 
@@ -577,6 +550,52 @@ template void launch_sweep_jobs<double>(const JobDesc*, int, const int*, int, in
                                         hipEvent_t, hipEvent_t);
 template void launch_sweep_jobs<float>(const JobDesc*, int, const int*, int, int, hipStream_t,
                                        hipEvent_t, hipEvent_t);
+
+// Two-pass form, second pass, after every kReplay iterations (kdev: the counter
+// after them): s += sum h_{k+1} r_{k+1} over the residuals in the ring, on the
+// vector grid.  Adding each residual in its own iteration read and wrote the
+// FP64 sum every time, 32 bytes per element against the 8 of an FP32 residual.
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_replay_sum(const JobDesc* __restrict__ jobs, int njobs,
+                                                       const int* __restrict__ kdev) {
+    const VecBlock v = vec_block(jobs, njobs);
+    const JobDesc& J = jobs[v.j];
+    constexpr int f = sizeof(R) == 4 ? 1 : 0;
+    if (J.phase != f) return;  // the other precision's job
+    const int k0 = (int)uniform((uint32_t)*kdev) - kReplay;
+    const int cnt = J.st[v.n].iter - k0;  // iterations of these that the source ran
+    if (cnt <= 0) return;
+    const int64_t n12 = 12 * J.g.Vt, off = (int64_t)v.n * n12;
+    const double2* h = J.h + (size_t)v.n * (J.sh.maxk + 1) + k0 + 1;
+    double2 c[kReplay];
+#pragma unroll
+    for (int i = 0; i < kReplay; ++i) c[i] = i < cnt ? h[i] : make_double2(0, 0);
+    const C2<R>* r = static_cast<const C2<R>*>(J.r[f]);
+    const int64_t rpp = (int64_t)J.rpp;
+    for (int64_t e = off + (int64_t)v.bx * kBlock + threadIdx.x; e < off + n12;
+         e += (int64_t)J.nbe * kBlock) {
+        cx<double> s = ld<double>(J.s64, e);
+        cx<R> rv[kReplay];
+#pragma unroll
+        for (int i = 0; i < kReplay; ++i)  // (k0 is a multiple of kReplay)
+            rv[i] = ld<R>(r, (int64_t)((1 + i) % kReplay) * rpp + e);
+#pragma unroll
+        for (int i = 0; i < kReplay; ++i)
+            if (i < cnt) {
+                s.re += c[i].x * (double)rv[i].re - c[i].y * (double)rv[i].im;
+                s.im += c[i].x * (double)rv[i].im + c[i].y * (double)rv[i].re;
+            }
+        stc<double>(J.s64, e, s);
+    }
+}
+template <typename R>
+void launch_replay_sum(const JobDesc* jobs, int njobs, const int* kdev, int vec_blocks_total,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_replay_sum<R>, dim3(vec_blocks_total), dim3(kBlock), 0, s, jobs, njobs,
+                       kdev);
+}
+template void launch_replay_sum<double>(const JobDesc*, int, const int*, int, hipStream_t);
+template void launch_replay_sum<float>(const JobDesc*, int, const int*, int, hipStream_t);
 
 // two-pass form, second pass: s = h_0 b (r_0 = b)
 __global__ __launch_bounds__(kBlock) void k_s_init(const double2* __restrict__ b,

@@ -117,6 +117,7 @@ struct ovl_ctx {
     DBuf jobs_dev;                         // batch lead: JobDesc table + iteration counter
     // chunk graphs by precision mode (1 FP64 jobs only, 2 FP32 only, 3 both)
     struct GraphCache { std::string key; hipGraphExec_t exec = nullptr; } graphs[3];
+    GraphCache second_graphs[3];           // the same for the two-pass form's second pass
     // per-kernel-class event timing (ovl_set_profiling)
     static constexpr int kClasses = 10;
     bool prof_on = false;
@@ -327,8 +328,9 @@ extern "C" int ovl_destroy(ovl_ctx* ctx) {
     for (DBuf* b : bufs) b->release();
     for (DBuf& b : ctx->slot_chunks) b.release();
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
-    for (auto& gc : ctx->graphs)
-        if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
+    for (auto* set : {ctx->graphs, ctx->second_graphs})
+        for (int i = 0; i < 3; ++i)
+            if (set[i].exec) (void)hipGraphExecDestroy(set[i].exec);
     if (ctx->ev_in) (void)hipEventDestroy(ctx->ev_in);
     if (ctx->ev_out) (void)hipEventDestroy(ctx->ev_out);
     if (ctx->ws) (void)hipStreamDestroy(ctx->ws);
@@ -1022,7 +1024,7 @@ struct Work {
     int k_switch;          // first basis slot (or iteration) held in FP32 (mixed), or -1
     int k_conv;            // iteration before which the job was converted to FP32, or -1
     int K;                 // seed iterations of the last solve (max over sources)
-    size_t rpp;            // elements between two r buffers (two-pass: 2, sweep forms: kSweep)
+    size_t rpp;            // elements between two r buffers
     int rmask;             // number of r buffers - 1
     double2* swc;          // sweep forms: coefficients and counts of the chunk (JobDesc)
     int* swn;
@@ -1080,11 +1082,11 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w, int64_t sites) {
     const size_t vec32 = (size_t)nsrc * N * sizeof(float2);
     const bool twopass = form == OVL_FORM_TWOPASS;
     const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
-    // r_k's buffers: r_k and r_{k+1} (two-pass), or every residual of a sweep
-    const size_t nr = twopass ? 2 : sweep ? kSweep : 1;
     w.split = split_iteration(ctx, sites);
     w.fused = w.split || (ctx->fused_iter == 1 && (form == OVL_FORM_BASIS || twopass));
     const size_t nq = w.fused ? 2 : 1;  // q buffers
+    // r_k's buffers: every residual of a sweep or of a replayed stretch
+    const size_t nr = twopass ? (w.fused ? 2 : kReplay) : sweep ? kSweep : 1;
     w.qpp = (size_t)nsrc * N;
     HIPCHK(ctx, ctx->b64.ensure(vec64));
     HIPCHK(ctx, ctx->r64.ensure(nr * vec64));
@@ -1276,6 +1278,7 @@ bool graphs_enabled(const ovl_ctx* ctx) {
 
 constexpr int kChunk = 16;  // seed iterations per captured graph / per convergence poll
 static_assert(kChunk == kSweep, "one shift sweep per chunk");
+static_assert(kChunk % kReplay == 0, "whole replayed stretches per chunk");
 // iteration i of a chunk reads the counter slot i & 1, so a chunk starts at slot 0
 static_assert(kChunk % 2 == 0, "chunks must hold an even number of iterations");
 
@@ -1292,6 +1295,9 @@ struct Batch {
     JobDesc* desc_dev = nullptr;
     int* kdev = nullptr;
     std::vector<char> retired;  // jobs taken out of the grids (every source finished)
+    // two-pass form's second pass of the two-kernel iteration: the residuals
+    // are added to the sum (second), the iteration is one kernel (replay)
+    bool second = false, replay = false;
 };
 
 void fill_desc(ovl_ctx* c, Work& w, JobDesc& d, const int (&variant)[2], const int (&lnk)[2],
@@ -1393,6 +1399,14 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
         }
         for (int f = 0; f < 2; ++f) {
             if (!(mode & (1 << f))) continue;
+            if (B.replay) {
+                ProfScope ps(lead, s, prof ? 0 + f : -1, 0.0);
+                if (f) launch_wilson_replay<float>(B.desc_dev, nj, kr, kw, B.sten_total[1], vars[1],
+                                                   B.lnk[1], s);
+                else launch_wilson_replay<double>(B.desc_dev, nj, kr, kw, B.sten_total[0], vars[0],
+                                                  B.lnk[0], s);
+                continue;
+            }
             // bytes credited after the solve from the sources' live iterations
             ProfScope ps(lead, s, prof ? 0 + f : -1, 0.0, true);
             if (f) launch_wilson_jobs<float>(B.desc_dev, nj, kr, B.sten_total[1], vars[1], B.lnk[1],
@@ -1400,7 +1414,7 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
             else launch_wilson_jobs<double>(B.desc_dev, nj, kr, B.sten_total[0], vars[0], B.lnk[0],
                                             s, ps.start(), ps.stop());
         }
-        for (int f = 0; f < 2; ++f) {
+        for (int f = 0; f < 2 && !B.replay; ++f) {
             if (!(mode & (1 << f))) continue;
             // K2: r update (r, q read, r written)
             ProfScope ps(lead, s, prof ? 2 + f : -1, 0.0, true);
@@ -1408,6 +1422,11 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
                                                   ps.start(), ps.stop());
             else launch_iteration_update<double>(B.desc_dev, nj, kr, kw, B.vec_total, s,
                                                  ps.start(), ps.stop());
+        }
+        for (int f = 0; f < 2 && B.second && (i + 1) % kReplay == 0; ++f) {
+            if (!(mode & (1 << f))) continue;
+            if (f) launch_replay_sum<float>(B.desc_dev, nj, kw, B.vec_total, s);
+            else launch_replay_sum<double>(B.desc_dev, nj, kw, B.vec_total, s);
         }
     }
     for (int f = 0; f < 2 && sweep; ++f) {
@@ -1433,8 +1452,8 @@ int replay_chunk(Batch& B, int mode, hipStream_t s) {
     snprintf(kb, sizeof(kb), "%p|%p|%zu|%d|%d|%d|%d|%d|%d|%d|%d|%d|%d", (void*)B.desc_dev,
              (void*)B.kdev, B.desc.size(), B.sten_total[0], B.sten_total[1], B.vec_total,
              B.variant64, B.variant32, B.form, B.sweep_units, B.lnk[0], B.lnk[1],
-             (int)B.fused + (int)B.split);
-    auto& gc = lead->graphs[mode - 1];
+             (int)B.fused + (int)B.split + 4 * (int)B.replay);
+    auto& gc = B.second ? lead->second_graphs[mode - 1] : lead->graphs[mode - 1];
     if (!gc.exec || gc.key != kb) {
         if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
         gc.exec = nullptr;
@@ -1632,7 +1651,9 @@ void credit_live_bytes(const Batch& B) {
                 mx = std::max(mx, itf);
             }
             lead->prof_bytes[0 + f] += V * es * (36.0 * sum + (B.lnk[f] ? 24.0 : 36.0) * mx);
-            lead->prof_bytes[2 + f] += 3.0 * 12.0 * V * es * sum;
+            // the replayed stencil also writes r_{k+1}; no update follows it
+            if (B.replay) lead->prof_bytes[0 + f] += 12.0 * V * es * sum;
+            else lead->prof_bytes[2 + f] += 3.0 * 12.0 * V * es * sum;
         }
     }
 }
@@ -2053,12 +2074,22 @@ static int solve_batch_once(Batch& B) {
             HIPCHK(c, hipGetLastError());
         }
         if (form == OVL_FORM_TWOPASS) {
-            // second pass: the same iterations again (bitwise identical, the
-            // reductions being deterministic), now adding h_{k+1} r_{k+1} to s
+            // second pass: the same iterations again, adding h_{k+1} r_{k+1} to s.
+            // Bitwise identical: with a replayable stencil the recorded scalars in
+            // the same arithmetic, keeping the first pass's state; otherwise, and in
+            // the one-kernel iterations, from the start again (their reductions
+            // are deterministic)
+            B.second = !B.fused;
+            B.replay = B.second && replayable(B.variant64) && (!mixed || replayable(B.variant32));
             for (size_t i = 0; i < B.w.size(); ++i) {
                 Work& w = *B.w[i];
-                rc = init_job(B.ctx[i], w, s);
-                if (rc) return rc;
+                if (B.replay) {
+                    HIPCHK(lead, hipMemcpyAsync(w.r64, w.b64, (size_t)w.nsrc * w.N * sizeof(double2),
+                                                hipMemcpyDeviceToDevice, s));
+                } else {
+                    rc = init_job(B.ctx[i], w, s);
+                    if (rc) return rc;
+                }
                 launch_s_init(w.b64, w.h, w.maxk, w.s64, w.N, w.nsrc, s);
                 B.desc[i].h = w.h;
                 B.desc[i].state_host = nullptr;  // the host keeps the first pass's final state
@@ -2093,6 +2124,7 @@ static int solve_batch_once(Batch& B) {
                 if (rc) return rc;
             }
             credit_live_bytes(B);  // the second pass repeats the same iterations
+            B.second = B.replay = false;
             HIPCHK(lead, hipGetLastError());
         }
     }

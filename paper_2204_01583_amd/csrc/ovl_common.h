@@ -158,6 +158,7 @@ struct ShiftDev {
 constexpr int kMaxJobs = 64;
 constexpr int kSlotChunk = 32;  // basis form: residual slots per allocation
 constexpr int kSweep = 16;      // sweep forms: seed iterations per shift sweep
+constexpr int kReplay = 8;      // two-pass form, second pass: iterations per addition to the sum
 // Grid blocks a job owns in a job-table stencil launch: its block count
 // padded to a multiple of 8 (one per XCD), so every job starts on XCD 0.
 inline __host__ __device__ int job_grid_blocks(int nb) { return (nb + 7) & ~7; }
@@ -183,7 +184,7 @@ struct JobDesc {
     void* q[2];
     void* r[2];                 // all but the basis form: r_k at r[..] + (k & rmask) * rpp
     size_t rpp;                 // elements between two r buffers
-    int rmask;                  // two-pass: 1 (two buffers); sweep forms: kSweep - 1
+    int rmask;                  // buffers - 1: two-pass kReplay - 1, sweep forms kSweep - 1
     double2* b64;               // packed source
     double2* s64;               // quadrature sum
     void* pj[2];                // sweep forms: [nsrc][J][12 Vt]
@@ -195,7 +196,7 @@ struct JobDesc {
                                 // by iteration k - 1; else 0
     char* const* slots;         // basis form: device table of slot-chunk bases
     size_t slot_bytes;          // bytes of one slot (nsrc * 12 Vt FP64 complex)
-    const double2* h;           // two-pass, second pass: h[src][i] weights of r_i
+    const double2* h;           // two-pass, second pass (replay): h[src][i] weights of r_i
     int ksw;                    // first FP32 iteration (slots from it hold FP32), or large
     int form;                   // OVL_FORM_* of this solve
     int phase;                  // precision of this job's iterations now: 0 FP64, 1 FP32 (the
@@ -208,6 +209,17 @@ struct JobDesc {
     char* state_host;           // device address of the pinned slots
     int state_bytes, state_stride;
 };
+
+// r' = r - alpha q of one element, with its rounding spelled out: the update
+// kernel and the replayed stencil must agree bit for bit
+template <typename R> __device__ __forceinline__ cx<R> sub_scaled(cx<R> r, R ar, R ai, cx<R> q) {
+    return {r.re - __builtin_fma(ar, q.re, -(ai * q.im)), r.im - __builtin_fma(ar, q.im, ai * q.re)};
+}
+template <> __device__ __forceinline__ cx<float> sub_scaled(cx<float> r, float ar, float ai,
+                                                            cx<float> q) {
+    return {r.re - __builtin_fmaf(ar, q.re, -(ai * q.im)),
+            r.im - __builtin_fmaf(ar, q.im, ai * q.re)};
+}
 
 // r_k and r_{k+1} of a job (element pointers of source 0; sources are 12 Vt apart)
 template <typename T>

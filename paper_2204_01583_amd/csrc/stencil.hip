@@ -260,7 +260,8 @@ __device__ __forceinline__ int plane_patch(int sb, const Geom& g, int nsb) {
 }
 
 // Body of the stencil for one block, `tile` being the block's position in
-// the (site tile, rhs group) space after the XCD-aware remap.
+// the (site tile, rhs group) space after the XCD-aware remap.  MODE 2: the
+// iteration replayed with its recorded scalars (k_wilson_replay).
 template <typename R, int MODE, int HPI, int RPT, int ORD, int SPL, int TIL, int LNK>
 __device__ __forceinline__ void wilson_block(const C2<R>* __restrict__ in, C2<R>* __restrict__ out,
                                              const C2<R>* __restrict__ U, const Geom& g, R kappa,
@@ -269,7 +270,7 @@ __device__ __forceinline__ void wilson_block(const C2<R>* __restrict__ in, C2<R>
                                              double4* __restrict__ partial,
                                              const SrcState* __restrict__ stt,
                                              const ShiftDev& sh, int k, int nsb, int nrhs,
-                                             unsigned tile) {
+                                             unsigned tile, const JobDesc* job = nullptr) {
     // ORD 0: rhs groups fastest, so the blocks of one site tile (all rhs) run
     // back to back on one XCD and share its links through L2 (few rhs).
     // ORD 1: site tiles fastest within an rhs group, so a tile's z and t
@@ -284,6 +285,7 @@ __device__ __forceinline__ void wilson_block(const C2<R>* __restrict__ in, C2<R>
     for (int r = 0; r < RPT; ++r) {
         on[r] = n0 + r < nrhs;
         if constexpr (MODE == 1) on[r] = on[r] && src_live(stt[n0 + r], sh, n0 + r, k);
+        if constexpr (MODE == 2) on[r] = on[r] && k < stt[n0 + r].iter;
         any = any || on[r];
     }
     if (!any) return;
@@ -365,6 +367,19 @@ __device__ __forceinline__ void wilson_block(const C2<R>* __restrict__ in, C2<R>
                     bi = (R)b.y;
                 }
             }
+            // replay: the recorded beta_{k-1} and alpha_k, and r_{k+1}'s buffer
+            R alr = 0, ali = 0;
+            C2<R>* rn = nullptr;
+            if constexpr (MODE == 2) {
+                const double2* sd = sh.seed + ((size_t)(n0 + r) * (sh.maxk + 1) + k) * 3;
+                if (k > 0) {
+                    br = (R)sd[-2].x;
+                    bi = (R)sd[-2].y;
+                }
+                alr = (R)sd[0].x;
+                ali = (R)sd[0].y;
+                rn = job_rk<C2<R>>(*job, k + 1, sizeof(R) == 4 ? 1 : 0) + (size_t)(n0 + r) * 12 * Vt;
+            }
             // every load of the site's own r_k and q_{k-1} is issued before the
             // first store: o may alias psi as far as the compiler knows, so a
             // load placed after a store would wait for it
@@ -382,7 +397,7 @@ __device__ __forceinline__ void wilson_block(const C2<R>* __restrict__ in, C2<R>
                         pv[ai][c] = ld<R>(psi[r], tix(comp, s, 12));
                     }
                     qv[ai][c] = mk<R>(0, 0);
-                    if constexpr (MODE == 1)
+                    if constexpr (MODE != 0)
                         if (k > 0) qv[ai][c] = ld<R>(o, tix(comp, s, 12));
                 }
             }
@@ -407,6 +422,10 @@ __device__ __forceinline__ void wilson_block(const C2<R>* __restrict__ in, C2<R>
                         q.re += br * qo.re - bi * qo.im;
                         q.im += br * qo.im + bi * qo.re;
                         stc<R>(o, tix(comp, s, 12), q);
+                        if constexpr (MODE == 2) {
+                            stc<R>(rn, tix(comp, s, 12), sub_scaled<R>(p, alr, ali, q));
+                            continue;
+                        }
                         // <r_k, q_k> = sum conj(r) q with r_k = p, accumulated in FP64
                         dre[r] += (double)p.re * (double)q.re + (double)p.im * (double)q.im;
                         dim[r] += (double)p.re * (double)q.im - (double)p.im * (double)q.re;
@@ -611,6 +630,31 @@ __global__ __launch_bounds__(kBlock * SPL) void k_wilson_jobs(const JobDesc* __r
                                       static_cast<const C2<R>*>(J.U[f]), J.g, (R)J.kappa, J.zs.x,
                                       J.zs.y, nullptr, J.part_w, J.st, J.sh, k, J.nsb, J.nsrc,
                                       tile);
+}
+
+// The two-pass form's second pass: the scalars of every iteration are on
+// record, so the stencil alone is the iteration.  It forms q_k with the same
+// expressions as k_wilson_jobs and r_{k+1} = r_k - alpha_k q_k in the update
+// kernel's arithmetic, so both passes' residuals agree bit for bit, needs no
+// reduction, and block 0 advances the counter.  Bound like the stencil; over
+// sixteen 8^4 x 4 jobs a second-pass iteration of stencil, update and a read
+// and write of the sum took 29 + 30 us (FP32) and 51 + 47 us (FP64), and this
+// with k_replay_sum cut the batch from 59.5 to 48 ms.
+template <typename R, int HPI, int LNK>
+__global__ __launch_bounds__(kBlock) void k_wilson_replay(const JobDesc* __restrict__ jobs, int njobs,
+                                                          const int* __restrict__ kread,
+                                                          int* __restrict__ kwrite) {
+    const int k = (int)uniform((uint32_t)*kread);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *kwrite = k + 1;
+    const int f = sizeof(R) == 4 ? 1 : 0;
+    int j;
+    unsigned tile;
+    if (!job_tile(jobs, njobs, f, j, tile)) return;
+    const JobDesc& J = jobs[j];
+    wilson_block<R, 2, HPI, 1, 0, 1, 1, LNK>(job_rk<const C2<R>>(J, k, f), static_cast<C2<R>*>(J.q[f]),
+                                             static_cast<const C2<R>*>(J.U[f]), J.g, (R)J.kappa,
+                                             J.zs.x, J.zs.y, nullptr, J.part_w, J.st, J.sh, k,
+                                             J.nsb, J.nsrc, tile, &J);
 }
 
 // ============================================================================
@@ -943,6 +987,24 @@ template void launch_wilson_jobs<double>(const JobDesc*, int, const int*, int, i
                                          hipEvent_t, hipEvent_t);
 template void launch_wilson_jobs<float>(const JobDesc*, int, const int*, int, int, int, hipStream_t,
                                         hipEvent_t, hipEvent_t);
+
+template <typename R>
+void launch_wilson_replay(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
+                          int total_blocks, int variant, int lnk, hipStream_t s) {
+    const dim3 grid(total_blocks), blk(kBlock);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, blk, 0, s, jobs, njobs, kread, kwrite); };
+    if (variant == 16) {
+        if (lnk) go(k_wilson_replay<R, 1, 1>);
+        else go(k_wilson_replay<R, 1, 0>);
+    } else {
+        if (lnk) go(k_wilson_replay<R, 2, 1>);
+        else go(k_wilson_replay<R, 2, 0>);
+    }
+}
+template void launch_wilson_replay<double>(const JobDesc*, int, const int*, int*, int, int, int,
+                                           hipStream_t);
+template void launch_wilson_replay<float>(const JobDesc*, int, const int*, int*, int, int, int,
+                                          hipStream_t);
 
 template <typename R, int HPI, int RPT, int ORD, int SPL, int TIL, int LNK>
 void launch_wilson_v(int mode, const C2<R>* in, C2<R>* out, const C2<R>* U, const Geom& g,

@@ -165,3 +165,30 @@ def test_hw_direct_matches_the_tiled_stencil(dims, nrhs, monkeypatch):
     ref = ctx.apply_hw(b)
     assert float((got - ref).abs().max() / ref.abs().max()) < 1e-14
     ctx.close()
+
+
+# The two-pass form's replayed second pass (LDS-tile variants 16 and 17) and the
+# repeated one (variant 0): the same s as the stored basis form, whose sum runs
+# over the same residuals in the same order, so a residual that differed in its
+# last bit would show.  Mixed, the slot converted at the switch is added from
+# its FP64 value, eps32 x 1e-3 of it away.  Padding sites, several sources,
+# iteration limits inside a stretch of 8.
+@pytest.mark.parametrize("links", ["two-row", "full"])
+@pytest.mark.parametrize("variant", [0, 16, 17])
+@pytest.mark.parametrize("precision,maxiter,tol", [(0, 4000, 1e-14), (0, 13, 1e-14), (1, 4000, 1e-12)])
+def test_two_pass_replay(variant, links, precision, maxiter, tol, monkeypatch):
+    monkeypatch.setenv("OVL_STENCIL_VARIANT", str(variant))
+    if links == "full":
+        monkeypatch.setenv("OVL_LINKS", "full")
+    dims, nsrc = (6, 6, 4, 6), 3
+    b = to_dev(si.gaussian_sources(dims, nsrc, first_seed=61))
+    out = []
+    for form in (2, 3):
+        ctx = make_ctx(dims, gauge(dims, 0.3, 6), nq=16, precision=precision, form=form, tol=1e-12,
+                       maxiter=maxiter, switch_res=1e-3)
+        for _ in range(2):  # the second solve replays the captured graphs
+            s, st = ctx.apply_sign(b, allow_not_converged=True)
+        assert precision == 0 or st.fp32_iterations > 0
+        out.append(s.cpu().numpy())
+        ctx.close()
+    assert_close(out[1], out[0], tol, f"variant {variant} {links} precision {precision}")
