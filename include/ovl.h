@@ -215,7 +215,11 @@ int ovl_apply_hw_noalloc(ovl_ctx* ctx, const void* in, void* out, int32_t nrhs);
  * its switch: `in` is rounded to complex64, the links are the context's FP32
  * copy, the arithmetic is FP32, and the result is widened to complex128 in
  * `out` (same layouts and argument rules as ovl_apply_hw).  For checking the
- * FP32 kernels; expect relative errors of order 1e-7. */
+ * FP32 kernels; expect relative errors of order 1e-7.  The tuner only picks
+ * among variants that agree bit for bit at the lattice and nrhs, so the result
+ * is the same on every call and context; OVL_STENCIL_VARIANT, OVL_AUTOTUNE=0
+ * and a choice stored in OVL_AUTOTUNE_CACHE select one variant whatever its
+ * rounding. */
 int ovl_apply_hw_fp32(ovl_ctx* ctx, const void* in, void* out, int32_t nrhs);
 
 /* out = sum_j c_j (z_j - H_W)^-1 in  (eqs. (5)-(7)) for nrhs spinors.

@@ -128,6 +128,8 @@ struct ovl_ctx {
     int64_t prof_n[kClasses] = {0};
     double prof_bytes[kClasses] = {0};
     // stencil variant chosen per (nrhs, precision + 2 mode) by the autotuner
+    // (+ kTuneOnly where only some choices are tried)
+    static constexpr int kTuneOnly = 8;
     std::map<std::pair<int, int>, int> stencil_variant;
     ovl_stats last{};
     char err[512] = {0};
@@ -666,14 +668,17 @@ static void stencil_store(ovl_ctx* ctx, int nrhs, int prec, int mode, int code) 
 // 1 FP32) and mode (0: H_W alone; 1: the solver's q_k = z_s r_k - H r_k +
 // beta q_{k-1} with its dot products, timed with every source live).  The
 // basis forms tune mode 1 inside the solve instead (tune_solver_stencil).
-static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode) {
+// only: the choices to try, where not all of them may be taken (kept apart
+// from the free choice of the same nrhs, prec and mode).
+static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode,
+                           const std::vector<int>* only = nullptr) {
     const int nfmt = ctx->links12 ? 2 : 1;  // link formats to try: full, and two-row if SU(3)
     const char* force = getenv("OVL_STENCIL_VARIANT");
     if (force && *force) {
         const int v = atoi(force);
         if (v >= 0 && v < kStencilVariants) return v + kStencilVariants * (nfmt - 1);
     }
-    const auto key = std::make_pair(nrhs, prec + 2 * mode);
+    const auto key = std::make_pair(nrhs, prec + 2 * mode + (only ? ovl_ctx::kTuneOnly : 0));
     auto it = ctx->stencil_variant.find(key);
     if (it != ctx->stencil_variant.end()) return it->second;
     const char* at = getenv("OVL_AUTOTUNE");
@@ -689,7 +694,10 @@ static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode) {
     }
     const size_t es = prec ? sizeof(float2) : sizeof(double2);
     const size_t nb = (size_t)nrhs * n12(ctx) * es;
-    int best = 0;
+    std::vector<int> codes;
+    if (only) codes = *only;
+    else for (int c = 0; c < kStencilVariants * nfmt; ++c) codes.push_back(c);
+    int best = codes[0];
     bool ok = ctx->bench_a.ensure(nb) == hipSuccess && ctx->bench_b.ensure(nb) == hipSuccess &&
               hipMemsetAsync(ctx->bench_a.p, 0, nb, ctx->stream) == hipSuccess;
     TuneInputs ti;
@@ -727,7 +735,7 @@ static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode) {
     const bool verbose = vb && vb[0] == '1';
     if (ok) {
         double tbest = 1e30;
-        for (int code = 0; code < kStencilVariants * nfmt; ++code) {
+        for (int code : codes) {
             const int v = code % kStencilVariants, lnk = code / kStencilVariants;
             const float2* U32 = lnk ? ctx->U32c.as<float2>() : ctx->U32.as<float2>();
             const double2* U64 = lnk ? ctx->U64c.as<double2>() : ctx->U64.as<double2>();
@@ -756,6 +764,49 @@ static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode) {
         write_cache(path, m);
     }
     return best;
+}
+
+// The choices that ovl_apply_hw_fp32 may take: variants of one summation
+// order in one link format, which agree bit for bit, so that its result does
+// not depend on which of them the tuner times as the fastest.  Variants with the
+// same lanes per site (1 or 2) and hops per step (1 or 2) sum the hops alike;
+// between such groups results are about 3e-8 apart.  The group is the one that
+// wins at the size (survey of 23 lattices x 7 source counts, kernel after a
+// cache flush, us; named lanes-hops, two-row links unless "full"):
+//   V = 64 x 1      full 2-2  8.7   2-2  9.6   2-1 10.7
+//   V = 180 x 3          2-2 10.6   2-1 11.5
+//   V = 480 x 4          2-1 12.4   2-2 12.7   1-2 14.7
+//   V = 4096 x 12        2-1 14.5   2-2 15.0   1-2 15.0
+//   V = 10080 x 6        2-2 15.0   2-1 15.2   1-2 15.7
+//   V = 65536 x 1        2-1 16.5   2-2 17.0   1-2 17.3
+//   V = 17280 x 4        1-2 18.5   1-1 19.4   2-1 22.5 (above 65536 in all)
+//   V = 131072 x 4       1-2 60.1   1-1 60.4
+//   V = 131072 x 12      1-1 143    1-2 150
+// full links (fields that are not SU(3)):
+//   V = 12960 x 2        2-2 15.4   1-2 15.6   2-1 15.6
+//   V = 12960 x 6        1-2 19.1   1-1 19.5   2-1 23.2
+//   V = 65536 x 6        1-1 47.4   1-2 51.3
+static std::vector<int> hw32_choices(const ovl_ctx* ctx, int nrhs) {
+    const int64_t V = ctx->g.V, sites = V * nrhs;
+    int lnk = ctx->links12 ? 1 : 0;
+    int lanes, hops;
+    if (sites > 65536) {  // every SIMD has a wave: one lane per site
+        lanes = 1;
+        hops = sites > (lnk ? 500000 : 131072) ? 1 : 2;
+    } else {
+        lanes = 2;
+        hops = !lnk || V < kBlock || (V > 4096 && nrhs >= 3 && sites > 40000) ? 2 : 1;
+        if (V <= kTile) lnk = 0;
+    }
+    // variant = 16 TIL + 8 (lanes - 1) + 4 ORD + 2 (RPT - 1) + (hops - 1); two
+    // lanes with two hops sum differently at two rhs per lane
+    std::vector<int> codes;
+    for (int v = 0; v < kShapeVariants; ++v) {
+        const bool two_rhs = (v >> 1) & 1;
+        if (((v >> 3) & 1) == lanes - 1 && (v & 1) == hops - 1 && !(lanes == 2 && hops == 2 && two_rhs))
+            codes.push_back(v + kStencilVariants * lnk);
+    }
+    return codes;
 }
 
 // Variant of the fused iteration kernel (code v + kIterVariants * links) for
@@ -986,7 +1037,8 @@ extern "C" int ovl_apply_hw_fp32(ovl_ctx* ctx, const void* in, void* out, int32_
     HIPCHK(ctx, ctx->hw_out.ensure(nb));
     launch_pack_spinor32(static_cast<const double2*>(in), ctx->hw_in.as<float2>(), ctx->g.V, ctx->g.Vt,
                          nrhs, ctx->stream);
-    const int code = stencil_variant(ctx, nrhs, 1, 0);
+    const std::vector<int> choices = hw32_choices(ctx, nrhs);
+    const int code = stencil_variant(ctx, nrhs, 1, 0, &choices);
     const int var = code % kStencilVariants, lnk = code / kStencilVariants;
     launch_wilson<float>(0, ctx->hw_in.as<float2>(), ctx->hw_out.as<float2>(),
                          stencil_links<float>(ctx, lnk), ctx->g, kappa_of(ctx->m0),
