@@ -127,9 +127,13 @@ struct ovl_ctx {
     double prof_ms[kClasses] = {0};
     int64_t prof_n[kClasses] = {0};
     double prof_bytes[kClasses] = {0};
-    // stencil variant chosen per (nrhs, precision + 2 mode) by the autotuner
-    // (+ kTuneOnly where only some choices are tried)
-    static constexpr int kTuneOnly = 8;
+    // stencil variant chosen by the autotuner per nrhs and precision + 2 mode
+    // (+ kTuneOnly where only some choices are tried, + kTuneTwoRow where the
+    // two-row links may be used: a choice holds for fields of its kind only)
+    static constexpr int kTuneOnly = 8, kTuneTwoRow = 16;
+    std::pair<int, int> choice_key(int nrhs, int what) const {
+        return {nrhs, what + (links12 ? kTuneTwoRow : 0)};
+    }
     std::map<std::pair<int, int>, int> stencil_variant;
     ovl_stats last{};
     char err[512] = {0};
@@ -637,7 +641,7 @@ static int stencil_lookup(ovl_ctx* ctx, int nrhs, int prec, int mode) {
         const int v = atoi(force);
         if (v >= 0 && v < kStencilVariants) return v + kStencilVariants * (nfmt - 1);
     }
-    const auto key = std::make_pair(nrhs, prec + 2 * mode);
+    const auto key = ctx->choice_key(nrhs, prec + 2 * mode);
     auto it = ctx->stencil_variant.find(key);
     if (it != ctx->stencil_variant.end()) return it->second;
     const char* at = getenv("OVL_AUTOTUNE");
@@ -654,7 +658,7 @@ static int stencil_lookup(ovl_ctx* ctx, int nrhs, int prec, int mode) {
 }
 
 static void stencil_store(ovl_ctx* ctx, int nrhs, int prec, int mode, int code) {
-    ctx->stencil_variant[std::make_pair(nrhs, prec + 2 * mode)] = code;
+    ctx->stencil_variant[ctx->choice_key(nrhs, prec + 2 * mode)] = code;
     const char* path = getenv("OVL_AUTOTUNE_CACHE");
     if (path && *path) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -678,7 +682,7 @@ static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode,
         const int v = atoi(force);
         if (v >= 0 && v < kStencilVariants) return v + kStencilVariants * (nfmt - 1);
     }
-    const auto key = std::make_pair(nrhs, prec + 2 * mode + (only ? ovl_ctx::kTuneOnly : 0));
+    const auto key = ctx->choice_key(nrhs, prec + 2 * mode + (only ? ovl_ctx::kTuneOnly : 0));
     auto it = ctx->stencil_variant.find(key);
     if (it != ctx->stencil_variant.end()) return it->second;
     const char* at = getenv("OVL_AUTOTUNE");
@@ -822,7 +826,7 @@ static int iter_variant(ovl_ctx* ctx, int nrhs, int prec) {
         const int v = atoi(force);
         if (v >= 0 && v < kIterVariants) return v + kIterVariants * (nfmt - 1);
     }
-    const auto key = std::make_pair(nrhs, prec + 4);
+    const auto key = ctx->choice_key(nrhs, prec + 4);
     auto it = ctx->stencil_variant.find(key);
     if (it != ctx->stencil_variant.end()) return it->second;
     const char* at = getenv("OVL_AUTOTUNE");

@@ -1,8 +1,11 @@
 """ovl_apply_hw_fp32 returns the same bits on every context: the tuner picks
 among stencil variants that sum the hops in one order."""
+import numpy as np
 import pytest
 
-from tests.gpu_util import gauge, make_ctx
+import seeded_inputs as si
+from oracle.wilson import hermitian_wilson
+from tests.gpu_util import assert_close, gauge, make_ctx, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +56,22 @@ def test_bits_do_not_depend_on_the_tuner(dims, nrhs, two, full, links, monkeypat
         ctx = make_ctx(dims, U)
         assert torch.equal(ctx.apply_hw_fp32(b), got[0]), f"variant {v}"
         ctx.close()
+
+
+# A field that is not SU(3) loaded where an SU(3) field was: the stored third
+# rows are read, not rebuilt; and back.
+def test_field_kind_changes_on_one_context():
+    dims = (6, 6, 4, 6)
+    b = to_dev(si.gaussian_sources(dims, 2, first_seed=59))
+    fields = [gauge(dims, 0.3, 6), 1.1 * gauge(dims, 0.3, 7), gauge(dims, 0.3, 8)]
+    ctx = make_ctx(dims, fields[0], nq=16, form=2)
+    ctx.set_residual_check(1)
+    for U in fields:
+        ctx.set_gauge(to_dev(U))
+        H = hermitian_wilson(U, 1.4)
+        ref = np.stack([(H @ v.ravel()).reshape(v.shape) for v in b.cpu().numpy()])
+        assert_close(ctx.apply_hw_fp32(b).cpu().numpy(), ref, 2e-6, "FP32")
+        # the residual check's operator is the solve's
+        _, st = ctx.apply_sign(b)
+        assert st.max_true_rel_res < 1e-11
+    ctx.close()
