@@ -1107,22 +1107,29 @@ const char* host_slot(const ovl_ctx* c, const Work& w, int slot) {
     return reinterpret_cast<const char*>(c->host_state) + (size_t)slot * state_slot_bytes(w);
 }
 
-// Whether a solve runs the split one-kernel iteration (split.hip):
-// where the whole solve has at most kSplitSites sites x sources, unless a
-// kernel is asked for by name.  Its one launch per iteration beats the two
+// Whether a solve of n contexts with nsrc[i] sources each runs the split
+// one-kernel iteration (split.hip): where the whole solve has at most
+// kSplitSites sites x sources, unless some context or the environment asks for
+// a kernel by name.  Its one launch per iteration beats the two
 // kernels' latency, its doubled neighbour loads lose to their bytes; per
 // iteration, two kernels / split, in us (FP64, FP32): 4096 sites 20.1 / 10.9,
 // 19.7 / 10.5; 16384 21.7 / 14.2, 20.7 / 13.5; 32768 24.9 / 23.1, 22.5 / 19.7;
 // 40960 27.6 / 27.8, 23.5 / 24.7; 65536 33.2 / 45.7, 26.4 / 38.2.
 constexpr int64_t kSplitSites = 36864;
-bool split_iteration(const ovl_ctx* ctx, int64_t sites) {
+bool split_iteration(ovl_ctx* const* ctxs, int n, const int* nsrc) {
     const char* force = getenv("OVL_STENCIL_VARIANT");
-    return ctx->fused_iter < 0 && !(force && *force) && sites <= kSplitSites;
+    if (force && *force) return false;
+    int64_t sites = 0;
+    for (int i = 0; i < n; ++i) {
+        if (ctxs[i]->fused_iter >= 0) return false;
+        sites += ctxs[i]->g.V * std::max(nsrc[i], 0);
+    }
+    return sites <= kSplitSites;
 }
 
-// Work buffers of a solve on ctx with nsrc sources; sites: the site x sources
-// of the whole (possibly batched) solve.
-int prepare(ovl_ctx* ctx, int nsrc, Work& w, int64_t sites) {
+// Work buffers of a solve on ctx with nsrc sources; split: the solve's
+// iteration (split_iteration).
+int prepare(ovl_ctx* ctx, int nsrc, Work& w, bool split) {
     const int J = (int)ctx->z.size();
     const int64_t N = n12(ctx);
     const bool mixed = ctx->precision == OVL_PREC_MIXED;
@@ -1138,7 +1145,7 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w, int64_t sites) {
     const size_t vec32 = (size_t)nsrc * N * sizeof(float2);
     const bool twopass = form == OVL_FORM_TWOPASS;
     const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
-    w.split = split_iteration(ctx, sites);
+    w.split = split;
     w.fused = w.split || (ctx->fused_iter == 1 && (form == OVL_FORM_BASIS || twopass));
     const size_t nq = w.fused ? 2 : 1;  // q buffers
     // r_k's buffers: every residual of a sweep or of a replayed stretch
@@ -2566,7 +2573,7 @@ static int apply_common(ovl_ctx* ctx, const void* in, void* out, int nrhs, ovl_s
     int rc = check_apply_args(ctx, in, out, nrhs, true);
     if (rc) return rc;
     Work w;
-    rc = prepare(ctx, nrhs, w, ctx->g.V * nrhs);
+    rc = prepare(ctx, nrhs, w, split_iteration(&ctx, 1, &nrhs));
     if (rc) return rc;
     launch_pack_spinor64(static_cast<const double2*>(in), w.b64, ctx->g.V, ctx->g.Vt, nrhs, ctx->stream);
     HIPCHK(ctx, hipGetLastError());
@@ -2653,7 +2660,9 @@ extern "C" int ovl_force(ovl_ctx* ctx, const void* phi, void* grad, int32_t kind
     //    kept implicit in the stored basis and coefficients
     ctx->form = OVL_FORM_BASIS;
     Work w;
-    rc = prepare(ctx, 1, w, ctx->g.V);
+    const int one = 1;
+    const bool split = split_iteration(&ctx, 1, &one);
+    rc = prepare(ctx, 1, w, split);
     if (rc) { restore(); return rc; }
     launch_pack_spinor64(static_cast<const double2*>(phi), w.b64, ctx->g.V, ctx->g.Vt, 1, s);
     const int rc1 = solve(ctx, w);
@@ -2692,7 +2701,7 @@ extern "C" int ovl_force(ovl_ctx* ctx, const void* phi, void* grad, int32_t kind
     swap_basis();
     for (int j = 0; j < J; ++j) ctx->z[j].y = -z0[j].y;
     Work w2;
-    rc = prepare(ctx, 1, w2, ctx->g.V);
+    rc = prepare(ctx, 1, w2, split);
     if (rc) { restore(); return rc; }
     HIPCHK(ctx, hipMemcpyAsync(w2.b64, ctx->fpsi.p, N * sizeof(double2), hipMemcpyDeviceToDevice, s));
     const int rc2 = solve(ctx, w2);
@@ -2779,11 +2788,10 @@ extern "C" int ovl_apply_sign_batched(ovl_ctx* const* ctxs, int32_t nctx, const 
     std::vector<Work> works(nctx);
     Batch B;
     int rc = OVL_OK;
-    int64_t sites = 0;
-    for (int i = 0; i < nctx; ++i) sites += ctxs[i]->g.V * std::max(nrhs[i], 0);
+    const bool split = split_iteration(ctxs, nctx, nrhs);
     for (int i = 0; i < nctx && rc == OVL_OK; ++i) {
         rc = check_apply_args(ctxs[i], in[i], out[i], nrhs[i], true);
-        if (rc == OVL_OK) rc = prepare(ctxs[i], nrhs[i], works[i], sites);
+        if (rc == OVL_OK) rc = prepare(ctxs[i], nrhs[i], works[i], split);
         if (rc != OVL_OK && ctxs[i] != lead) {
             fail(lead, rc, "context %d: %s", i, ctxs[i]->err);
         }
