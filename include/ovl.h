@@ -74,10 +74,13 @@ extern "C" {
 
 #define OVL_FORM_REFERENCE 0 /* per-shift solutions x_j kept in HBM, s = sum c_j x_j at the end */
 #define OVL_FORM_FUSED     1 /* per-shift directions p_j only; s accumulated in the same sweep
-                                (both: one sweep per 16 iterations, over 16 residual buffers)   */
+                                (both: one sweep per 16 iterations, over 16 residual buffers, or
+                                per iteration over one where the solve would take more than half of
+                                the free memory)                                             */
 #define OVL_FORM_BASIS     2 /* seed residuals r_k stored; s = sum_k h_k r_k from the scalars    */
 #define OVL_FORM_TWOPASS   3 /* as BASIS without storing the r_k: a second pass regenerates them
-                                bit for bit (deterministic reductions) and accumulates s       */
+                                bit for bit (deterministic reductions) and accumulates s, from 8
+                                residual buffers, or 2 under the same condition              */
 
 typedef struct ovl_ctx ovl_ctx;
 

@@ -82,12 +82,13 @@ template <typename R>
 void launch_iteration_update(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
                              int vec_blocks_total, hipStream_t s, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
-// sweep forms, after every kSweep iterations: the shifted directions and the
-// sum (or the shifted solutions) advanced by all of them; kdev is the
-// iteration counter after the last one, units the largest sweep_units of a job
+// sweep forms, after every `window` iterations (kSweep, or 1 with residuals
+// updated in place): the shifted directions and the sum (or the shifted
+// solutions) advanced by all of them; kdev is the iteration counter after the
+// last one, units the largest sweep_units of a job
 template <typename R>
 void launch_sweep_jobs(const JobDesc* jobs, int njobs, const int* kdev, int units, int form,
-                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                       int window, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int sweep_units(int64_t n12, int nsrc);
 // The fused one-kernel seed iteration of the basis forms (stencil.hip): kernel
 // k forms r_k and q_k = A r_k + beta q_{k-1} without the direction p, and
@@ -114,10 +115,11 @@ void launch_set_phase(JobDesc* job, int phase, hipStream_t s);
 // read from kdev (the iteration counter after a chunk)
 void launch_export_state(const JobDesc* jobs, int njobs, const int* kdev, int chunk,
                          hipStream_t s);
-// two-pass form, second pass: s += h r over the last kReplay residuals
+// two-pass form, second pass: s += h r over the last `window` residuals
+// (kReplay, or 2)
 template <typename R>
 void launch_replay_sum(const JobDesc* jobs, int njobs, const int* kdev, int vec_blocks_total,
-                       hipStream_t s);
+                       int window, hipStream_t s);
 // two-pass form, second pass: s = h_0 b
 void launch_s_init(const double2* b, const double2* h, int maxk, double2* s, int64_t n12, int nsrc,
                    hipStream_t st);

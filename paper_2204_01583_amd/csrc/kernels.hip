@@ -246,7 +246,7 @@ void launch_convert_64_to_32(const double2* a, float2* b, int64_t n, hipStream_t
 //       alpha^j, beta^j, residual estimates and deactivation (blocks
 //       0..nslices-1 own one 256-shift slice each, one lane per shift), then
 //       r_{k+1} = r_k - alpha_k q_k.
-// The sweep forms add a third kernel after every kSweep iterations, which
+// The sweep forms add a third kernel after every kSweep iterations (or every one), which
 // advances the shifted directions and the sum by all of them (k_sweep_jobs).
 // Quantities written in iteration k live in parity (k&1) or mod-3 buffers, so
 // no block reads what another block of the same kernel writes:
@@ -397,11 +397,11 @@ template void launch_iteration_update<double>(const JobDesc*, int, const int*, i
 template void launch_iteration_update<float>(const JobDesc*, int, const int*, int*, int,
                                              hipStream_t, hipEvent_t, hipEvent_t);
 
-// The shift sweep of the last kSweep iterations k0 .. k0 + kSweep - 1 whose
+// The shift sweep of the last W iterations k0 .. k0 + W - 1 whose
 // shifts have been advanced (in the one-kernel iteration the chunk's last
 // kernel has advanced them by the iteration before its own, lag = 1, so the
 // first window starts at -1), for every shift j active in some of them, from
-// the residuals r_{k0+1} ..  (still in their ring of kSweep buffers) and the
+// the residuals r_{k0+1} ..  (still in their ring of W buffers) and the
 // recorded coefficients (swc[.][i] = (coefficient, 1/pi_{k+1}^j, beta^j) of
 // iteration k = k0 + i, swn = the iterations shift j took part in):
 //   fused:     s += c_j alpha^j p_j,   reference: x_j += alpha^j p_j;   then
@@ -415,7 +415,9 @@ template void launch_iteration_update<float>(const JobDesc*, int, const int*, in
 // A block takes 64 elements, its four waves every fourth active shift, so a
 // lattice of a few hundred sites still spreads; their sums meet in LDS in wave
 // order.
-template <typename R, bool REF>
+// W = 1 (one r buffer, updated in place) is for solves that leave no room for
+// kSweep residuals: it moves kSweep times the bytes.
+template <typename R, bool REF, int W>
 __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict__ jobs,
                                                        const int* __restrict__ kdev) {
     constexpr int NW = kBlock / 64;
@@ -427,7 +429,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
     const int n = (int)blockIdx.x / per;
     if (n >= J.nsrc) return;
     const int lag = J.lag;
-    const int k0 = (int)uniform((uint32_t)*kdev) - kSweep - lag;
+    const int k0 = (int)uniform((uint32_t)*kdev) - W - lag;
     if (J.st[n].iter <= (k0 > 0 ? k0 : 0)) return;  // finished before this window
     const ShiftDev& sh = J.sh;
     const int lane = (int)(threadIdx.x & 63), w = (int)uniform(threadIdx.x >> 6);
@@ -458,10 +460,10 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
     const int64_t ve = (int64_t)n * n12 + e;
     const C2<R>* rbase = static_cast<const C2<R>*>(J.r[f]);
     const int64_t rpp = (int64_t)J.rpp;
-    cx<R> r[kSweep];
+    cx<R> r[W];
 #pragma unroll
-    for (int i = 0; i < kSweep; ++i)  // (k0 + lag is a multiple of kSweep)
-        r[i] = ld<R>(rbase, (int64_t)((1 + i - lag) & (kSweep - 1)) * rpp + ve);
+    for (int i = 0; i < W; ++i)  // (k0 + lag is a multiple of W)
+        r[i] = ld<R>(rbase, (int64_t)((1 + i - lag) & (W - 1)) * rpp + ve);
     const bool first = k0 <= 0;
     cx<R> b0 = mk<R>(0, 0);
     if (first) {
@@ -484,7 +486,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
         cx<R> p = pnext;
         if (l + step < nl && !first)  // the next shift's direction, in flight meanwhile
             pnext = ld<R>(pj, ((int64_t)n * sh.J + (int)uniform((uint32_t)l_j[l + step])) * n12 + e);
-        const Cst cf = (Cst)(const double*)(J.swc + ((size_t)n * sh.J + j) * kSweep * 3);
+        const Cst cf = (Cst)(const double*)(J.swc + ((size_t)n * sh.J + j) * W * 3);
         cx<double> x = mk<double>(0, 0);
         if constexpr (REF) x = ld<double>(J.xj, o);
         double tre = 0.0, tim = 0.0;
@@ -500,13 +502,13 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
         // four iterations at a time, their scalar loads together; a shift
         // that stopped within the four takes them one by one
 #pragma unroll
-        for (int g = 0; g < kSweep; g += 4) {
-            if (cnt >= g + 4) {
+        for (int g = 0; g < W; g += 4) {
+            if (W >= 4 && cnt >= g + 4) {
 #pragma unroll
-                for (int i = g; i < g + 4; ++i) step_of(i);
+                for (int i = g; i < g + 4 && i < W; ++i) step_of(i);
             } else if (cnt > g) {
 #pragma unroll
-                for (int i = g; i < g + 3; ++i)
+                for (int i = g; i < g + 3 && i < W; ++i)
                     if (cnt > i) step_of(i);
             }
         }
@@ -537,50 +539,56 @@ __global__ __launch_bounds__(kBlock) void k_sweep_jobs(const JobDesc* __restrict
 int sweep_units(int64_t n12, int nsrc) { return (int)(n12 / 64) * nsrc; }
 template <typename R>
 void launch_sweep_jobs(const JobDesc* jobs, int njobs, const int* kdev, int units, int form,
-                       hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                       int window, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const dim3 grid((unsigned)units, (unsigned)njobs), blk(kBlock);
     auto go = [&](auto kern) {
         if (ev0) hipExtLaunchKernelGGL(kern, grid, blk, 0, s, ev0, ev1, 0, jobs, kdev);
         else hipLaunchKernelGGL(kern, grid, blk, 0, s, jobs, kdev);
     };
-    if (form == OVL_FORM_REFERENCE) go(k_sweep_jobs<R, true>);
-    else go(k_sweep_jobs<R, false>);
+    const bool ref = form == OVL_FORM_REFERENCE;
+    if (window == kSweep) {
+        if (ref) go(k_sweep_jobs<R, true, kSweep>);
+        else go(k_sweep_jobs<R, false, kSweep>);
+    } else {
+        if (ref) go(k_sweep_jobs<R, true, 1>);
+        else go(k_sweep_jobs<R, false, 1>);
+    }
 }
-template void launch_sweep_jobs<double>(const JobDesc*, int, const int*, int, int, hipStream_t,
+template void launch_sweep_jobs<double>(const JobDesc*, int, const int*, int, int, int, hipStream_t,
                                         hipEvent_t, hipEvent_t);
-template void launch_sweep_jobs<float>(const JobDesc*, int, const int*, int, int, hipStream_t,
+template void launch_sweep_jobs<float>(const JobDesc*, int, const int*, int, int, int, hipStream_t,
                                        hipEvent_t, hipEvent_t);
 
-// Two-pass form, second pass, after every kReplay iterations (kdev: the counter
+// Two-pass form, second pass, after every W iterations (kdev: the counter
 // after them): s += sum h_{k+1} r_{k+1} over the residuals in the ring, on the
 // vector grid.  Adding each residual in its own iteration read and wrote the
 // FP64 sum every time, 32 bytes per element against the 8 of an FP32 residual.
-template <typename R>
+template <typename R, int W>
 __global__ __launch_bounds__(kBlock) void k_replay_sum(const JobDesc* __restrict__ jobs, int njobs,
                                                        const int* __restrict__ kdev) {
     const VecBlock v = vec_block(jobs, njobs);
     const JobDesc& J = jobs[v.j];
     constexpr int f = sizeof(R) == 4 ? 1 : 0;
     if (J.phase != f) return;  // the other precision's job
-    const int k0 = (int)uniform((uint32_t)*kdev) - kReplay;
+    const int k0 = (int)uniform((uint32_t)*kdev) - W;
     const int cnt = J.st[v.n].iter - k0;  // iterations of these that the source ran
     if (cnt <= 0) return;
     const int64_t n12 = 12 * J.g.Vt, off = (int64_t)v.n * n12;
     const double2* h = J.h + (size_t)v.n * (J.sh.maxk + 1) + k0 + 1;
-    double2 c[kReplay];
+    double2 c[W];
 #pragma unroll
-    for (int i = 0; i < kReplay; ++i) c[i] = i < cnt ? h[i] : make_double2(0, 0);
+    for (int i = 0; i < W; ++i) c[i] = i < cnt ? h[i] : make_double2(0, 0);
     const C2<R>* r = static_cast<const C2<R>*>(J.r[f]);
     const int64_t rpp = (int64_t)J.rpp;
     for (int64_t e = off + (int64_t)v.bx * kBlock + threadIdx.x; e < off + n12;
          e += (int64_t)J.nbe * kBlock) {
         cx<double> s = ld<double>(J.s64, e);
-        cx<R> rv[kReplay];
+        cx<R> rv[W];
 #pragma unroll
-        for (int i = 0; i < kReplay; ++i)  // (k0 is a multiple of kReplay)
-            rv[i] = ld<R>(r, (int64_t)((1 + i) % kReplay) * rpp + e);
+        for (int i = 0; i < W; ++i)  // (k0 is a multiple of W)
+            rv[i] = ld<R>(r, (int64_t)((1 + i) % W) * rpp + e);
 #pragma unroll
-        for (int i = 0; i < kReplay; ++i)
+        for (int i = 0; i < W; ++i)
             if (i < cnt) {
                 s.re += c[i].x * (double)rv[i].re - c[i].y * (double)rv[i].im;
                 s.im += c[i].x * (double)rv[i].im + c[i].y * (double)rv[i].re;
@@ -590,12 +598,15 @@ __global__ __launch_bounds__(kBlock) void k_replay_sum(const JobDesc* __restrict
 }
 template <typename R>
 void launch_replay_sum(const JobDesc* jobs, int njobs, const int* kdev, int vec_blocks_total,
-                       hipStream_t s) {
-    hipLaunchKernelGGL(k_replay_sum<R>, dim3(vec_blocks_total), dim3(kBlock), 0, s, jobs, njobs,
-                       kdev);
+                       int window, hipStream_t s) {
+    const dim3 grid(vec_blocks_total), blk(kBlock);
+    if (window == kReplay)
+        hipLaunchKernelGGL((k_replay_sum<R, kReplay>), grid, blk, 0, s, jobs, njobs, kdev);
+    else
+        hipLaunchKernelGGL((k_replay_sum<R, 2>), grid, blk, 0, s, jobs, njobs, kdev);
 }
-template void launch_replay_sum<double>(const JobDesc*, int, const int*, int, hipStream_t);
-template void launch_replay_sum<float>(const JobDesc*, int, const int*, int, hipStream_t);
+template void launch_replay_sum<double>(const JobDesc*, int, const int*, int, int, hipStream_t);
+template void launch_replay_sum<float>(const JobDesc*, int, const int*, int, int, hipStream_t);
 
 // two-pass form, second pass: s = h_0 b (r_0 = b)
 __global__ __launch_bounds__(kBlock) void k_s_init(const double2* __restrict__ b,

@@ -1127,9 +1127,65 @@ bool split_iteration(ovl_ctx* const* ctxs, int n, const int* nsrc) {
     return sites <= kSplitSites;
 }
 
-// Work buffers of a solve on ctx with nsrc sources; split: the solve's
-// iteration (split_iteration).
-int prepare(ovl_ctx* ctx, int nsrc, Work& w, bool split) {
+// What a solve runs, decided once for all its contexts.
+struct Plan {
+    bool split;  // the split one-kernel iteration
+    bool ring;   // sweep and two-pass forms: a ring of residuals (kSweep, kReplay) and one sweep or
+                 // addition to the sum per turn of it; else 1 or 2 buffers and one per 1 or 2
+                 // iterations
+};
+
+// The ring makes these forms' passes over the directions and the sum rare (12^4 x
+// 2, 2 x 64 nodes, fused form: 15.4 against 48.9 ms with a sweep inside every
+// update), but takes 15 (sweep) or 6 (two-pass) more vectors per source and
+// precision, which with a few shifts is most of the memory.  It is used where
+// the whole solve takes at most half of the memory that is free, so that a
+// solve that fits without it always fits; a solve that has its buffers asks for
+// nothing.
+Plan plan_solve(ovl_ctx* const* ctxs, int n, const int* nsrc) {
+    Plan P{split_iteration(ctxs, n, nsrc), true};
+    const int form = ctxs[0]->form;
+    const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
+    if (!sweep && form != OVL_FORM_TWOPASS) return P;
+    double need = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const ovl_ctx* c = ctxs[i];
+        const double J = (double)c->z.size(), ns = std::max(nsrc[i], 0);
+        const double v64 = ns * (double)n12(c) * sizeof(double2), v32 = v64 / 2;
+        const double nr = sweep ? kSweep : P.split ? 2 : kReplay, nq = P.split ? 2 : 1;
+        auto grow = [&](const DBuf& b, double bytes) { need += std::max(bytes - (double)b.bytes, 0.0); };
+        for (const DBuf* b : {&c->b64, &c->p64, &c->s64}) grow(*b, v64);
+        grow(c->r64, nr * v64);
+        grow(c->q64, nq * v64);
+        if (sweep) grow(c->pj64, J * v64);
+        if (form == OVL_FORM_REFERENCE) grow(c->xj, J * v64);
+        if (c->precision == OVL_PREC_MIXED) {
+            grow(c->r32, nr * v32);
+            grow(c->q32, nq * v32);
+            if (sweep) grow(c->pj32, J * v32);
+        }
+        if (!sweep) {
+            const double hs = ns * (c->maxiter + 1.0) * J * sizeof(double2);
+            grow(c->hist, 3 * hs);
+            grow(c->W, hs);
+        }
+    }
+    if (need > 0.0) {
+        size_t avail = 0, total = 0;
+        if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+            (void)hipGetLastError();
+            avail = 0;
+        }
+        P.ring = need <= 0.5 * (double)avail;
+    }
+    // (the split iteration needs r_{k-1} beside r_k; with one buffer the
+    // stencil and update kernels run)
+    if (sweep && !P.ring) P.split = false;
+    return P;
+}
+
+// Work buffers of a solve on ctx with nsrc sources.
+int prepare(ovl_ctx* ctx, int nsrc, Work& w, const Plan& plan) {
     const int J = (int)ctx->z.size();
     const int64_t N = n12(ctx);
     const bool mixed = ctx->precision == OVL_PREC_MIXED;
@@ -1145,11 +1201,13 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w, bool split) {
     const size_t vec32 = (size_t)nsrc * N * sizeof(float2);
     const bool twopass = form == OVL_FORM_TWOPASS;
     const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
-    w.split = split;
+    w.split = plan.split;
     w.fused = w.split || (ctx->fused_iter == 1 && (form == OVL_FORM_BASIS || twopass));
     const size_t nq = w.fused ? 2 : 1;  // q buffers
     // r_k's buffers: every residual of a sweep or of a replayed stretch
-    const size_t nr = twopass ? (w.fused ? 2 : kReplay) : sweep ? kSweep : 1;
+    const size_t nr = twopass ? (w.fused || !plan.ring ? 2 : kReplay)
+                      : sweep ? (plan.ring ? kSweep : 1)
+                              : 1;
     w.qpp = (size_t)nsrc * N;
     HIPCHK(ctx, ctx->b64.ensure(vec64));
     HIPCHK(ctx, ctx->r64.ensure(nr * vec64));
@@ -1178,7 +1236,7 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w, bool split) {
         w.q32 = ctx->q32.as<float2>();
     }
     if (sweep) {
-        const size_t nc = (size_t)nsrc * J * kSweep * 3;
+        const size_t nc = (size_t)nsrc * J * nr * 3;
         HIPCHK(ctx, ctx->sweep.ensure(nc * sizeof(double2) + (size_t)nsrc * J * sizeof(int)));
         w.swc = ctx->sweep.as<double2>();
         w.swn = reinterpret_cast<int*>(w.swc + nc);
@@ -1293,6 +1351,29 @@ int prepare(ovl_ctx* ctx, int nsrc, Work& w, bool split) {
     return OVL_OK;
 }
 
+// Work buffers of a solve of n contexts.  Should the ring not fit after all,
+// every context gives its buffers back and takes the small ones.  On an error,
+// *at is the context that has its message.
+int prepare_solve(ovl_ctx* const* ctxs, int n, const int* nsrc, Work* const* w, int* at) {
+    Plan plan = plan_solve(ctxs, n, nsrc);
+    for (;;) {
+        int rc = OVL_OK;
+        for (int i = 0; i < n && rc == OVL_OK; ++i) {
+            rc = prepare(ctxs[i], nsrc[i], *w[i], plan);
+            *at = i;
+        }
+        const int form = ctxs[0]->form;
+        if (rc != OVL_E_OOM || form == OVL_FORM_BASIS || !plan.ring) return rc;
+        (void)hipGetLastError();
+        for (int i = 0; i < n; ++i) {
+            ctxs[i]->r64.release();
+            ctxs[i]->r32.release();
+        }
+        plan.ring = false;
+        if (form != OVL_FORM_TWOPASS) plan.split = false;
+    }
+}
+
 template <typename R> R* slot_ptr(const Work& w, int i) {
     return reinterpret_cast<R*>(w.chunks[i / kSlotChunk] + (size_t)(i % kSlotChunk) * w.slot_bytes);
 }
@@ -1340,7 +1421,7 @@ bool graphs_enabled(const ovl_ctx* ctx) {
 }
 
 constexpr int kChunk = 16;  // seed iterations per captured graph / per convergence poll
-static_assert(kChunk == kSweep, "one shift sweep per chunk");
+static_assert(kChunk % kSweep == 0, "whole shift sweeps per chunk");
 static_assert(kChunk % kReplay == 0, "whole replayed stretches per chunk");
 // iteration i of a chunk reads the counter slot i & 1, so a chunk starts at slot 0
 static_assert(kChunk % 2 == 0, "chunks must hold an even number of iterations");
@@ -1361,6 +1442,8 @@ struct Batch {
     // two-pass form's second pass of the two-kernel iteration: the residuals
     // are added to the sum (second), the iteration is one kernel (replay)
     bool second = false, replay = false;
+    // iterations per shift sweep (sweep forms) or per addition to the sum (second)
+    int window = 1;
 };
 
 void fill_desc(ovl_ctx* c, Work& w, JobDesc& d, const int (&variant)[2], const int (&lnk)[2],
@@ -1425,13 +1508,13 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
     const bool sweep = B.form == OVL_FORM_FUSED || B.form == OVL_FORM_REFERENCE;
     double sweep_b[2] = {0, 0};
     if (prof && sweep) {
-        // the residuals of the chunk and s read once, s written; p_j of the active
+        // the residuals of the sweep and s read once, s written; p_j of the active
         // shifts read and written (and x_j in the reference form)
         const bool ref = B.form == OVL_FORM_REFERENCE;
         for (size_t i = 0; i < B.w.size(); ++i) {
             const int f = B.desc[i].phase;
             const double es = f ? sizeof(float2) : sizeof(double2);
-            sweep_b[f] += 12.0 * (double)B.ctx[i]->g.V * B.w[i]->nsrc * (kSweep * es + (ref ? 0.0 : 32.0));
+            sweep_b[f] += 12.0 * (double)B.ctx[i]->g.V * B.w[i]->nsrc * (B.window * es + (ref ? 0.0 : 32.0));
         }
         const int f0 = B.desc[0].phase;
         const double es0 = f0 ? sizeof(float2) : sizeof(double2);
@@ -1439,6 +1522,16 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
     }
     const int vars[2] = {B.variant64, B.variant32};
     const int nj = (int)B.desc.size();
+    auto shift_sweep = [&](const int* kd) {
+        for (int f = 0; f < 2; ++f) {
+            if (!(mode & (1 << f))) continue;
+            ProfScope ps(lead, s, prof ? 4 + f : -1, sweep_b[f], true);
+            if (f) launch_sweep_jobs<float>(B.desc_dev, nj, kd, B.sweep_units, B.form, B.window, s,
+                                            ps.start(), ps.stop());
+            else launch_sweep_jobs<double>(B.desc_dev, nj, kd, B.sweep_units, B.form, B.window, s,
+                                           ps.start(), ps.stop());
+        }
+    };
     for (int i = 0; i < count; ++i) {
         int* kr = B.kdev + (i & 1);
         int* kw = B.kdev + ((i + 1) & 1);
@@ -1458,6 +1551,7 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
                 else launch_iter_jobs<double>(B.desc_dev, nj, kr, kw, B.sten_total[0], vars[0],
                                               B.lnk[0], s, ps.start(), ps.stop());
             }
+            if (sweep && (i + 1) % B.window == 0) shift_sweep(kw);
             continue;
         }
         for (int f = 0; f < 2; ++f) {
@@ -1486,20 +1580,12 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
             else launch_iteration_update<double>(B.desc_dev, nj, kr, kw, B.vec_total, s,
                                                  ps.start(), ps.stop());
         }
-        for (int f = 0; f < 2 && B.second && (i + 1) % kReplay == 0; ++f) {
+        for (int f = 0; f < 2 && B.second && (i + 1) % B.window == 0; ++f) {
             if (!(mode & (1 << f))) continue;
-            if (f) launch_replay_sum<float>(B.desc_dev, nj, kw, B.vec_total, s);
-            else launch_replay_sum<double>(B.desc_dev, nj, kw, B.vec_total, s);
+            if (f) launch_replay_sum<float>(B.desc_dev, nj, kw, B.vec_total, B.window, s);
+            else launch_replay_sum<double>(B.desc_dev, nj, kw, B.vec_total, B.window, s);
         }
-    }
-    for (int f = 0; f < 2 && sweep; ++f) {
-        if (!(mode & (1 << f))) continue;
-        int* kd = B.kdev + (count & 1);
-        ProfScope ps(lead, s, prof ? 4 + f : -1, sweep_b[f], true);
-        if (f) launch_sweep_jobs<float>(B.desc_dev, nj, kd, B.sweep_units, B.form, s, ps.start(),
-                                        ps.stop());
-        else launch_sweep_jobs<double>(B.desc_dev, nj, kd, B.sweep_units, B.form, s, ps.start(),
-                                       ps.stop());
+        if (sweep && (i + 1) % B.window == 0) shift_sweep(kw);
     }
     // the chunk's final state to the pinned host slots (the counter after an
     // even number of iterations is in slot 0)
@@ -1512,10 +1598,10 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
 int replay_chunk(Batch& B, int mode, hipStream_t s) {
     ovl_ctx* lead = B.ctx[0];
     char kb[256];
-    snprintf(kb, sizeof(kb), "%p|%p|%zu|%d|%d|%d|%d|%d|%d|%d|%d|%d|%d", (void*)B.desc_dev,
+    snprintf(kb, sizeof(kb), "%p|%p|%zu|%d|%d|%d|%d|%d|%d|%d|%d|%d|%d|%d", (void*)B.desc_dev,
              (void*)B.kdev, B.desc.size(), B.sten_total[0], B.sten_total[1], B.vec_total,
              B.variant64, B.variant32, B.form, B.sweep_units, B.lnk[0], B.lnk[1],
-             (int)B.fused + (int)B.split + 4 * (int)B.replay);
+             (int)B.fused + (int)B.split + 4 * (int)B.replay, B.window);
     auto& gc = B.second ? lead->second_graphs[mode - 1] : lead->graphs[mode - 1];
     if (!gc.exec || gc.key != kb) {
         if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
@@ -1907,6 +1993,7 @@ static int solve_batch_once(Batch& B) {
     for (ovl_ctx* c : B.ctx) all12 = all12 && c->links12;
     B.fused = B.w[0]->fused;
     B.split = B.w[0]->split;
+    B.window = B.w[0]->rmask + 1;
     for (Work* w : B.w)
         if (w->fused != B.fused || w->split != B.split)
             return fail(lead, OVL_E_ARG, "mixed iteration kinds in one batch");
@@ -2573,7 +2660,9 @@ static int apply_common(ovl_ctx* ctx, const void* in, void* out, int nrhs, ovl_s
     int rc = check_apply_args(ctx, in, out, nrhs, true);
     if (rc) return rc;
     Work w;
-    rc = prepare(ctx, nrhs, w, split_iteration(&ctx, 1, &nrhs));
+    Work* wp = &w;
+    int at = 0;
+    rc = prepare_solve(&ctx, 1, &nrhs, &wp, &at);
     if (rc) return rc;
     launch_pack_spinor64(static_cast<const double2*>(in), w.b64, ctx->g.V, ctx->g.Vt, nrhs, ctx->stream);
     HIPCHK(ctx, hipGetLastError());
@@ -2661,8 +2750,8 @@ extern "C" int ovl_force(ovl_ctx* ctx, const void* phi, void* grad, int32_t kind
     ctx->form = OVL_FORM_BASIS;
     Work w;
     const int one = 1;
-    const bool split = split_iteration(&ctx, 1, &one);
-    rc = prepare(ctx, 1, w, split);
+    const Plan plan = plan_solve(&ctx, 1, &one);
+    rc = prepare(ctx, 1, w, plan);
     if (rc) { restore(); return rc; }
     launch_pack_spinor64(static_cast<const double2*>(phi), w.b64, ctx->g.V, ctx->g.Vt, 1, s);
     const int rc1 = solve(ctx, w);
@@ -2701,7 +2790,7 @@ extern "C" int ovl_force(ovl_ctx* ctx, const void* phi, void* grad, int32_t kind
     swap_basis();
     for (int j = 0; j < J; ++j) ctx->z[j].y = -z0[j].y;
     Work w2;
-    rc = prepare(ctx, 1, w2, split);
+    rc = prepare(ctx, 1, w2, plan);
     if (rc) { restore(); return rc; }
     HIPCHK(ctx, hipMemcpyAsync(w2.b64, ctx->fpsi.p, N * sizeof(double2), hipMemcpyDeviceToDevice, s));
     const int rc2 = solve(ctx, w2);
@@ -2788,17 +2877,19 @@ extern "C" int ovl_apply_sign_batched(ovl_ctx* const* ctxs, int32_t nctx, const 
     std::vector<Work> works(nctx);
     Batch B;
     int rc = OVL_OK;
-    const bool split = split_iteration(ctxs, nctx, nrhs);
+    int at = 0;
     for (int i = 0; i < nctx && rc == OVL_OK; ++i) {
+        at = i;
         rc = check_apply_args(ctxs[i], in[i], out[i], nrhs[i], true);
-        if (rc == OVL_OK) rc = prepare(ctxs[i], nrhs[i], works[i], split);
-        if (rc != OVL_OK && ctxs[i] != lead) {
-            fail(lead, rc, "context %d: %s", i, ctxs[i]->err);
-        }
         B.ctx.push_back(ctxs[i]);
         B.w.push_back(&works[i]);
     }
-    if (rc != OVL_OK) { restore(); return rc; }
+    if (rc == OVL_OK) rc = prepare_solve(ctxs, nctx, nrhs, B.w.data(), &at);
+    if (rc != OVL_OK) {
+        if (ctxs[at] != lead) fail(lead, rc, "context %d: %s", at, ctxs[at]->err);
+        restore();
+        return rc;
+    }
     for (int i = 0; i < nctx; ++i)
         launch_pack_spinor64(static_cast<const double2*>(in[i]), works[i].b64, ctxs[i]->g.V, ctxs[i]->g.Vt, nrhs[i],
                              lead->stream);

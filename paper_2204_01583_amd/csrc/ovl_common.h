@@ -157,8 +157,9 @@ struct ShiftDev {
 // one launch advances every job of a batch by one stage.
 constexpr int kMaxJobs = 64;
 constexpr int kSlotChunk = 32;  // basis form: residual slots per allocation
-constexpr int kSweep = 16;      // sweep forms: seed iterations per shift sweep
-constexpr int kReplay = 8;      // two-pass form, second pass: iterations per addition to the sum
+constexpr int kSweep = 16;      // sweep forms: seed iterations per shift sweep, or 1
+constexpr int kReplay = 8;      // two-pass form, second pass: iterations per addition to the sum,
+                                // or 2; the smaller of each where memory is short (plan_solve)
 // Grid blocks a job owns in a job-table stencil launch: its block count
 // padded to a multiple of 8 (one per XCD), so every job starts on XCD 0.
 inline __host__ __device__ int job_grid_blocks(int nb) { return (nb + 7) & ~7; }
@@ -184,14 +185,15 @@ struct JobDesc {
     void* q[2];
     void* r[2];                 // all but the basis form: r_k at r[..] + (k & rmask) * rpp
     size_t rpp;                 // elements between two r buffers
-    int rmask;                  // buffers - 1: two-pass kReplay - 1, sweep forms kSweep - 1
+    int rmask;                  // buffers - 1: the iterations per addition to the sum (two-pass) or
+                                // per shift sweep, less 1
     double2* b64;               // packed source
     double2* s64;               // quadrature sum
     void* pj[2];                // sweep forms: [nsrc][J][12 Vt]
     double2* xj;                // reference form
-    double2* swc;               // sweep forms: [nsrc][J][kSweep][3] coefficients of the chunk's
+    double2* swc;               // sweep forms: [nsrc][J][rmask + 1][3] coefficients of the sweep's
                                 // iterations (see k_sweep_jobs)
-    int* swn;                   // sweep forms: [nsrc][J] iterations of the chunk shift j was active in
+    int* swn;                   // sweep forms: [nsrc][J] iterations of the sweep shift j was active in
     int lag;                    // 1 in the one-kernel iterations, whose kernel k advances the shifts
                                 // by iteration k - 1; else 0
     char* const* slots;         // basis form: device table of slot-chunk bases

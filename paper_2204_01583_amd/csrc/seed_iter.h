@@ -113,9 +113,9 @@ __device__ __forceinline__ void advance_shift_slice(const JobDesc& J, const SrcS
             sh.h_pi[ho + sh.J] = act ? t.pn : make_double2(1, 0);
         }
         if (J.swc != nullptr) {
-            const int at = (i + J.lag) % kSweep;
+            const int at = (i + J.lag) & J.rmask;
             if (act) {
-                double2* w = J.swc + (o * kSweep + at) * 3;
+                double2* w = J.swc + (o * (size_t)(J.rmask + 1) + at) * 3;
                 w[0] = J.form == OVL_FORM_REFERENCE ? t.aj : cmul(sh.c[j], t.aj);
                 w[1] = t.ipi;
                 w[2] = t.bj;

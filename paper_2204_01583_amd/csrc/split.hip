@@ -97,7 +97,7 @@ __device__ __forceinline__ void iter_split_block(const JobDesc& J, int k, unsign
             const int j = b * kBlock + (int)threadIdx.x;
             if (J.swc != nullptr && threadIdx.x < kBlock && j < sh.J) {
                 const size_t o = (size_t)n * sh.J + j;
-                double2* c = J.swc + o * kSweep * 3;
+                double2* c = J.swc + o * (size_t)(J.rmask + 1) * 3;
                 c[0] = c[1] = make_double2(0, 0);
                 c[2] = make_double2(1, 0);
                 J.swn[o] = 1;
