@@ -106,7 +106,11 @@ typedef struct {
 /* Create a context for a Lx*Ly*Lz*Lt lattice on HIP device `device`.
  * dims = {Lx, Ly, Lz, Lt}, each >= 2; bc = {+1|-1} per direction (paper: the
  * boundary is not stated; the usual choice is {1,1,1,-1}).  `hip_stream` is a
- * hipStream_t or NULL for the null stream.  *ctx receives the context. */
+ * hipStream_t or NULL for the null stream.  *ctx receives the context.
+ * ovl_apply_hw takes every lattice that fits in memory; the solver's stencils
+ * (ovl_apply_sign, ovl_apply_dov, ovl_force, batches; ovl_apply_hw_fp32) use
+ * 32-bit offsets within a source and return OVL_E_ARG beyond 22369621 sites
+ * (FP64, and mixed) or 44739242 (FP32 alone). */
 int ovl_create(ovl_ctx** ctx, const int32_t dims[4], const int32_t bc[4],
                int32_t device, void* hip_stream);
 int ovl_destroy(ovl_ctx* ctx);

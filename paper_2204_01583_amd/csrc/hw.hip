@@ -56,7 +56,9 @@ __device__ __forceinline__ cx<R> add_phase(cx<R> a, R sgn, cx<R> b, R s1, R s3) 
     else return mk<R>(a.re + f * b.re, a.im + f * b.im);
 }
 
-template <int LNK>
+// WIDE: 64-bit byte offsets, for lattices on which 32 bits do not reach every
+// site (offsets32).
+template <int LNK, bool WIDE>
 __global__ __launch_bounds__(kBlock, 2) void k_hw_quad(const double2* __restrict__ in,
                                                        double2* __restrict__ out,
                                                        const double2* __restrict__ U, Geom g,
@@ -81,10 +83,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_hw_quad(const double2* __restrict
     coord[1] = (int)(rem % (uint32_t)g.L[1]); rem /= (uint32_t)g.L[1];
     coord[2] = (int)(rem % (uint32_t)g.L[2]);
     coord[3] = (int)(rem / (uint32_t)g.L[2]);
+    typedef typename std::conditional<WIDE, int64_t, uint32_t>::type Off;
     const double2* src = in + (size_t)n * 12 * V;
     auto spin = [&](uint32_t site, cx<R> (&v)[3]) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = ld<R>(src, site * 12u + 3u * a + (uint32_t)c);
+        for (int c = 0; c < 3; ++c) v[c] = ld<R>(src, (Off)site * 12u + 3u * a + (uint32_t)c);
+    };
+    auto link = [](uint32_t e, uint32_t site) -> Off {
+        if constexpr (WIDE) return tix64(e, site, NE);
+        else return tix(e, site, NE);
     };
     cx<R> acc[3] = {mk<R>(0, 0), mk<R>(0, 0), mk<R>(0, 0)};
     auto direction = [&](auto muc) {
@@ -95,7 +102,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_hw_quad(const double2* __restrict
         const double2* Um = U + (size_t)MU * NE * Vt;
         cx<R> m[3][3], v[3], w[3];
 #pragma unroll
-        for (uint32_t e = 0; e < NE; ++e) m[e / 3][e % 3] = ld<R>(Um, tix(e, ls, NE));
+        for (uint32_t e = 0; e < NE; ++e) m[e / 3][e % 3] = ld<R>(Um, link(e, ls));
         spin(nw, w);
         spin(nv, v);
         if constexpr (LNK == 1) {
@@ -147,7 +154,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_hw_quad(const double2* __restrict
         // D psi = psi - kappa acc ; H = gamma5 D
         cx<R> hv = p[c] - kappa * acc[c];
         if (!up) hv = -hv;
-        stc<R>(o, s * 12u + 3u * a + (uint32_t)c, hv);
+        stc<R>(o, (Off)s * 12u + 3u * a + (uint32_t)c, hv);
     }
 }
 
@@ -161,10 +168,16 @@ void launch_hw(const double2* in, double2* out, const double2* U, const Geom& g,
     const int order = (size_t)g.V * nrhs * 12 * sizeof(double2) > ((size_t)192 << 20);
     const unsigned ntile = (unsigned)((g.V + kBlock / 4 - 1) / (kBlock / 4));
     const dim3 grid(ntile * (unsigned)nrhs);
-    if (lnk)
-        hipLaunchKernelGGL(k_hw_quad<1>, grid, dim3(kBlock), 0, s, in, out, U, g, kappa, nrhs, order);
-    else
-        hipLaunchKernelGGL(k_hw_quad<0>, grid, dim3(kBlock), 0, s, in, out, U, g, kappa, nrhs, order);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(kBlock), 0, s, in, out, U, g, kappa, nrhs, order);
+    };
+    if (offsets32(g.Vt, sizeof(double2))) {
+        if (lnk) go(k_hw_quad<1, false>);
+        else go(k_hw_quad<0, false>);
+    } else {
+        if (lnk) go(k_hw_quad<1, true>);
+        else go(k_hw_quad<0, true>);
+    }
 }
 
 }  // namespace ovl

@@ -975,6 +975,14 @@ static int check_apply_args(ovl_ctx* ctx, const void* in, const void* out, int n
     return OVL_OK;
 }
 
+// Refuses lattices beyond the tiled kernels' 32-bit offsets (elements of es bytes).
+static int check_tiled(ovl_ctx* ctx, size_t es) {
+    if (offsets32(ctx->g.Vt, es)) return OVL_OK;
+    return fail(ctx, OVL_E_ARG, "%lld sites are more than the %s stencil's %lld",
+                (long long)ctx->g.V, es == sizeof(double2) ? "FP64" : "FP32",
+                (long long)(((uint64_t)1 << 32) / (12 * es)));
+}
+
 // OVL_STENCIL_VARIANT asks for one of the tiled stencil's variants, which H_W
 // alone then goes through (pack, stencil, unpack)
 static bool stencil_forced() {
@@ -999,6 +1007,8 @@ extern "C" int ovl_apply_hw(ovl_ctx* ctx, const void* in, void* out, int32_t nrh
         HIPCHK(ctx, hipGetLastError());
         return OVL_OK;
     }
+    rc = check_tiled(ctx, sizeof(double2));
+    if (rc) return rc;
     const size_t nb = (size_t)nrhs * n12(ctx) * sizeof(double2);
     HIPCHK(ctx, ctx->hw_in.ensure(nb));
     HIPCHK(ctx, ctx->hw_out.ensure(nb));
@@ -1035,6 +1045,8 @@ extern "C" int ovl_apply_hw_fp32(ovl_ctx* ctx, const void* in, void* out, int32_
     if (!ctx) return OVL_E_ARG;
     DeviceGuard dg(ctx->device);
     int rc = check_apply_args(ctx, in, out, nrhs, false);
+    if (rc) return rc;
+    rc = check_tiled(ctx, sizeof(float2));
     if (rc) return rc;
     const size_t nb = (size_t)nrhs * n12(ctx) * sizeof(float2);
     HIPCHK(ctx, ctx->hw_in.ensure(nb));
@@ -1186,6 +1198,8 @@ Plan plan_solve(ovl_ctx* const* ctxs, int n, const int* nsrc) {
 
 // Work buffers of a solve on ctx with nsrc sources.
 int prepare(ovl_ctx* ctx, int nsrc, Work& w, const Plan& plan) {
+    const int rct = check_tiled(ctx, sizeof(double2));
+    if (rct) return rct;
     const int J = (int)ctx->z.size();
     const int64_t N = n12(ctx);
     const bool mixed = ctx->precision == OVL_PREC_MIXED;
@@ -2939,6 +2953,8 @@ extern "C" int ovl_bench_kernel(ovl_ctx* ctx, int32_t which, int32_t nrhs, int32
     const int64_t N = n12(ctx);
     const bool f32 = which == 1 || which >= 200;
     const size_t es = f32 ? sizeof(float2) : sizeof(double2);
+    const int rct = check_tiled(ctx, es);
+    if (rct) return rct;
     const size_t nb = (size_t)nrhs * N * es;
     const int code = explicit_v ? which % 100 : stencil_variant(ctx, nrhs, f32 ? 1 : 0, 0);
     const int var = code % kStencilVariants, lnk = code / kStencilVariants;

@@ -86,6 +86,13 @@ template <typename R> __device__ __forceinline__ void fmac_(cx<R>& a, cx<R> b, c
     a.im += b.re * c.im - b.im * c.re;
 }
 
+// Whether 32-bit byte offsets reach every element of one source's tiled vector
+// of es-byte elements (and of one direction's links, which are smaller): the
+// lattices the tiled kernels take, 22.3 million sites in FP64, 44.7 in FP32.
+constexpr bool offsets32(int64_t Vt, size_t es) {
+    return (uint64_t)12 * (uint64_t)Vt * es <= (uint64_t)1 << 32;
+}
+
 // Lattice geometry of one context.  Sites are numbered
 // s = x + Lx*(y + Ly*(z + Lz*t)).  Internal fields are tiled over 64-site
 // tiles (see tix): a spinor is [rhs][Vt/64][12][64] (component 3*spin +
