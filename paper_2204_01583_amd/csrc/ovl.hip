@@ -210,7 +210,7 @@ struct DeviceGuard {
     }
 };
 
-// Times one launch of class `cls` (profiling only): by default two marker
+// Times one launch of class `cls` (profiling only; none for cls < 0): by default two marker
 // events bracket the launch; with kernel_events the caller hands start() and
 // stop() to a hipExtLaunchKernel launch instead, which stamps them with the
 // kernel's own start and end, free of the markers' dispatch overhead.
@@ -221,7 +221,7 @@ struct ProfScope {
     bool ext;
     ProfScope(ovl_ctx* c, hipStream_t s, int cls, double bytes, bool kernel_events = false)
         : ctx(c), st(s), ext(kernel_events) {
-        if (!ctx->prof_on) return;
+        if (!ctx->prof_on || cls < 0) return;
         const size_t need = 2 * (ctx->prof_pending.size() + 1);
         while (ctx->ev_pool.size() < need) {
             hipEvent_t e;
