@@ -319,11 +319,13 @@ int ovl_bench_kernel(ovl_ctx* ctx, int32_t which, int32_t nrhs, int32_t reps,
  * summed duration, the number of launches and the summed algorithmic bytes
  * since the last ovl_set_profiling(ctx, 1).  kclass:
  *   0 stencil FP64 (q = z_s p - H p with <r,q>,   1 the same in FP32
- *     ||q||^2 and ||r||^2)
+ *     ||q||^2 and ||r||^2; two-pass form, second
+ *     pass: q and the next r)
  *   2 r update FP64                                3 the same in FP32
  *   4 shift sweep FP64 (fused and reference        5 the same in FP32
  *     forms, one per 16 iterations)
- *   6 basis sum s = sum h_k r_k                    7 scalar kernels
+ *   6 basis sum s = sum h_k r_k (two-pass form:    7 scalar kernels
+ *     the second pass's additions to s)
  *   8 fused iteration FP64 (basis forms: r_k and   9 the same in FP32
  *     q_k = A r_k + beta q_{k-1} in one kernel)
  * Algorithmic bytes count every array element the kernel must read or write

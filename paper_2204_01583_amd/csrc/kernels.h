@@ -75,7 +75,8 @@ void launch_wilson_jobs(const JobDesc* jobs, int njobs, const int* kdev, int tot
 inline bool replayable(int variant) { return variant == 16 || variant == 17; }
 template <typename R>
 void launch_wilson_replay(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
-                          int total_blocks, int variant, int lnk, hipStream_t s);
+                          int total_blocks, int variant, int lnk, hipStream_t s,
+                          hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // K2: seed and shift scalars, shift bookkeeping, r update; reads the iteration
 // index from kread and writes its successor to kwrite
 template <typename R>
@@ -119,7 +120,8 @@ void launch_export_state(const JobDesc* jobs, int njobs, const int* kdev, int ch
 // (kReplay, or 2)
 template <typename R>
 void launch_replay_sum(const JobDesc* jobs, int njobs, const int* kdev, int vec_blocks_total,
-                       int window, hipStream_t s);
+                       int window, hipStream_t s, hipEvent_t ev0 = nullptr,
+                       hipEvent_t ev1 = nullptr);
 // two-pass form, second pass: s = h_0 b
 void launch_s_init(const double2* b, const double2* h, int maxk, double2* s, int64_t n12, int nsrc,
                    hipStream_t st);

@@ -598,15 +598,19 @@ __global__ __launch_bounds__(kBlock) void k_replay_sum(const JobDesc* __restrict
 }
 template <typename R>
 void launch_replay_sum(const JobDesc* jobs, int njobs, const int* kdev, int vec_blocks_total,
-                       int window, hipStream_t s) {
+                       int window, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const dim3 grid(vec_blocks_total), blk(kBlock);
-    if (window == kReplay)
-        hipLaunchKernelGGL((k_replay_sum<R, kReplay>), grid, blk, 0, s, jobs, njobs, kdev);
-    else
-        hipLaunchKernelGGL((k_replay_sum<R, 2>), grid, blk, 0, s, jobs, njobs, kdev);
+    auto go = [&](auto kern) {
+        if (ev0) hipExtLaunchKernelGGL(kern, grid, blk, 0, s, ev0, ev1, 0, jobs, njobs, kdev);
+        else hipLaunchKernelGGL(kern, grid, blk, 0, s, jobs, njobs, kdev);
+    };
+    if (window == kReplay) go(k_replay_sum<R, kReplay>);
+    else go(k_replay_sum<R, 2>);
 }
-template void launch_replay_sum<double>(const JobDesc*, int, const int*, int, int, hipStream_t);
-template void launch_replay_sum<float>(const JobDesc*, int, const int*, int, int, hipStream_t);
+template void launch_replay_sum<double>(const JobDesc*, int, const int*, int, int, hipStream_t,
+                                        hipEvent_t, hipEvent_t);
+template void launch_replay_sum<float>(const JobDesc*, int, const int*, int, int, hipStream_t,
+                                       hipEvent_t, hipEvent_t);
 
 // two-pass form, second pass: s = h_0 b (r_0 = b)
 __global__ __launch_bounds__(kBlock) void k_s_init(const double2* __restrict__ b,

@@ -1571,11 +1571,11 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
         for (int f = 0; f < 2; ++f) {
             if (!(mode & (1 << f))) continue;
             if (B.replay) {
-                ProfScope ps(lead, s, prof ? 0 + f : -1, 0.0);
+                ProfScope ps(lead, s, prof ? 0 + f : -1, 0.0, true);
                 if (f) launch_wilson_replay<float>(B.desc_dev, nj, kr, kw, B.sten_total[1], vars[1],
-                                                   B.lnk[1], s);
+                                                   B.lnk[1], s, ps.start(), ps.stop());
                 else launch_wilson_replay<double>(B.desc_dev, nj, kr, kw, B.sten_total[0], vars[0],
-                                                  B.lnk[0], s);
+                                                  B.lnk[0], s, ps.start(), ps.stop());
                 continue;
             }
             // bytes credited after the solve from the sources' live iterations
@@ -1596,8 +1596,11 @@ void enqueue_chunk(const Batch& B, int mode, int count, hipStream_t s, bool prof
         }
         for (int f = 0; f < 2 && B.second && (i + 1) % B.window == 0; ++f) {
             if (!(mode & (1 << f))) continue;
-            if (f) launch_replay_sum<float>(B.desc_dev, nj, kw, B.vec_total, B.window, s);
-            else launch_replay_sum<double>(B.desc_dev, nj, kw, B.vec_total, B.window, s);
+            ProfScope ps(lead, s, prof ? 6 : -1, 0.0, true);
+            if (f) launch_replay_sum<float>(B.desc_dev, nj, kw, B.vec_total, B.window, s,
+                                            ps.start(), ps.stop());
+            else launch_replay_sum<double>(B.desc_dev, nj, kw, B.vec_total, B.window, s,
+                                           ps.start(), ps.stop());
         }
         if (sweep && (i + 1) % B.window == 0) shift_sweep(kw);
     }
@@ -1804,19 +1807,22 @@ void credit_live_bytes(const Batch& B) {
         }
         for (int f = 0; f < 2; ++f) {
             const double es = f ? (double)sizeof(float2) : (double)sizeof(double2);
-            double sum = 0.0;
+            double sum = 0.0, windows = 0.0;
             int mx = 0;
             for (int n = 0; n < w.nsrc; ++n) {
                 const int it = std::min(hs[n].iter, w.maxk);
                 const int n64 = k_switch < 0 ? it : std::min(it, k_switch);
                 const int itf = f ? it - n64 : n64;
                 sum += itf;
+                windows += (itf + B.window - 1) / B.window;
                 mx = std::max(mx, itf);
             }
             lead->prof_bytes[0 + f] += V * es * (36.0 * sum + (B.lnk[f] ? 24.0 : 36.0) * mx);
             // the replayed stencil also writes r_{k+1}; no update follows it
             if (B.replay) lead->prof_bytes[0 + f] += 12.0 * V * es * sum;
             else lead->prof_bytes[2 + f] += 3.0 * 12.0 * V * es * sum;
+            // the second pass's sum: every residual read, s read and written per window
+            if (B.second) lead->prof_bytes[6] += 12.0 * V * (es * sum + 32.0 * windows);
         }
     }
 }

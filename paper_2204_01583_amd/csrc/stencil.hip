@@ -990,9 +990,15 @@ template void launch_wilson_jobs<float>(const JobDesc*, int, const int*, int, in
 
 template <typename R>
 void launch_wilson_replay(const JobDesc* jobs, int njobs, const int* kread, int* kwrite,
-                          int total_blocks, int variant, int lnk, hipStream_t s) {
+                          int total_blocks, int variant, int lnk, hipStream_t s, hipEvent_t ev0,
+                          hipEvent_t ev1) {
     const dim3 grid(total_blocks), blk(kBlock);
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, blk, 0, s, jobs, njobs, kread, kwrite); };
+    auto go = [&](auto kern) {
+        if (ev0)
+            hipExtLaunchKernelGGL(kern, grid, blk, 0, s, ev0, ev1, 0, jobs, njobs, kread, kwrite);
+        else
+            hipLaunchKernelGGL(kern, grid, blk, 0, s, jobs, njobs, kread, kwrite);
+    };
     if (variant == 16) {
         if (lnk) go(k_wilson_replay<R, 1, 1>);
         else go(k_wilson_replay<R, 1, 0>);
@@ -1002,9 +1008,9 @@ void launch_wilson_replay(const JobDesc* jobs, int njobs, const int* kread, int*
     }
 }
 template void launch_wilson_replay<double>(const JobDesc*, int, const int*, int*, int, int, int,
-                                           hipStream_t);
+                                           hipStream_t, hipEvent_t, hipEvent_t);
 template void launch_wilson_replay<float>(const JobDesc*, int, const int*, int*, int, int, int,
-                                          hipStream_t);
+                                          hipStream_t, hipEvent_t, hipEvent_t);
 
 template <typename R, int HPI, int RPT, int ORD, int SPL, int TIL, int LNK>
 void launch_wilson_v(int mode, const C2<R>* in, C2<R>* out, const C2<R>* U, const Geom& g,
