@@ -1052,6 +1052,51 @@ __global__ __launch_bounds__(kBlock, 2) void k_materialize(char* const* __restri
                     stc<double>(Y, (int64_t)j * n12 + e + 16 * q, mk<double>(re[m][q][r], im[m][q][r]));
         }
 }
+// The same sums for up to JG shifts (the residual check's one, small force
+// chunks), one thread per element on vector instructions: with few shifts the
+// basis is all there is to read, and the matrix form's rows for 16 shifts are
+// padding.  Per launch at 16^4, matrix form / this, in us (FP64, mixed): 1 shift
+// 531 / 496, 437 / 379; 4 shifts 554 / 523, 459 / 429.
+template <int JG>
+__global__ __launch_bounds__(kBlock) void k_materialize_few(char* const* __restrict__ chunks,
+                                                            size_t slot_bytes, int K, int ksw,
+                                                            const double2* __restrict__ W, int J,
+                                                            int j0, int jn, double2* __restrict__ Y,
+                                                            int64_t n12, int64_t eoff) {
+    typedef double __attribute__((ext_vector_type(2))) D2;
+    typedef float __attribute__((ext_vector_type(2))) F2;
+    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (e >= n12) return;
+    double re[JG], im[JG];
+#pragma unroll
+    for (int q = 0; q < JG; ++q) re[q] = im[q] = 0.0;
+    auto add = [&](int i, double vr, double vi) {
+#pragma unroll
+        for (int q = 0; q < JG; ++q)
+            if (q < jn) {
+                const double2 u = W[(int64_t)i * J + j0 + q];
+                re[q] += u.x * vr - u.y * vi;
+                im[q] += u.x * vi + u.y * vr;
+            }
+    };
+    auto slot = [&](int i) {
+        return (const OVL_GLOBAL char*)chunks[i / kSlotChunk] + (size_t)(i % kSlotChunk) * slot_bytes;
+    };
+    const int k64 = ksw < K ? ksw : K;
+#pragma unroll 4
+    for (int i = 0; i < k64; ++i) {
+        const D2 v = ((const OVL_GLOBAL D2*)slot(i))[eoff + e];
+        add(i, v.x, v.y);
+    }
+#pragma unroll 4
+    for (int i = k64; i < K; ++i) {
+        const F2 v = ((const OVL_GLOBAL F2*)slot(i))[eoff + e];
+        add(i, (double)v.x, (double)v.y);
+    }
+#pragma unroll
+    for (int q = 0; q < JG; ++q)
+        if (q < jn) stc<double>(Y, (int64_t)q * n12 + e, mk<double>(re[q], im[q]));
+}
 void launch_materialize(char* const* chunks, size_t slot_bytes, int K, int ksw, const double2* W,
                         int J, int j0, int jn, double2* Y, int64_t n12, int64_t eoff,
                         hipStream_t s) {
@@ -1065,6 +1110,15 @@ void launch_materialize(char* const* chunks, size_t slot_bytes, int K, int ksw, 
     };
     if (K < 1) {  // no slot: the sums are empty
         (void)hipMemsetAsync(Y, 0, (size_t)jn * n12 * sizeof(double2), s);
+        return;
+    }
+    // few shifts on a lattice that fills the chip with one element per thread;
+    // below, the matrix form's split of the slots over lanes wins (matrix / this,
+    // us: 12^4 x 4 shifts, mixed, 163 / 183; 8^4 x 1 44 / 111)
+    if (jn <= 4 && n12 >= 1536 * kBlock) {
+        const dim3 grid((unsigned)((n12 + kBlock - 1) / kBlock));
+        hipLaunchKernelGGL(k_materialize_few<4>, grid, dim3(kBlock), 0, s, chunks, slot_bytes, K,
+                           ksw, W, J, j0, jn, Y, n12, eoff);
         return;
     }
     using std::integral_constant;
