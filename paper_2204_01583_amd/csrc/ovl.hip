@@ -41,9 +41,10 @@ struct DBuf {
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // the fill, not other streams' work
         if (e == hipSuccess) {
             bytes = nb;
-        } else if (p) {
-            (void)hipFree(p);
+        } else {
+            if (p) (void)hipFree(p);
             p = nullptr;
+            (void)hipGetLastError();  // reported here, not by the caller's next launch
         }
         return e;
     }
@@ -154,9 +155,11 @@ int fail(ovl_ctx* ctx, int code, const char* fmt, ...) {
 #define HIPCHK(ctx, call)                                                                   \
     do {                                                                                    \
         hipError_t e_ = (call);                                                             \
-        if (e_ != hipSuccess)                                                               \
+        if (e_ != hipSuccess) {                                                             \
+            (void)hipGetLastError(); /* reported here, not by the caller's next launch */   \
             return fail((ctx), e_ == hipErrorOutOfMemory ? OVL_E_OOM : OVL_E_HIP,           \
-                        "%s failed: %s", #call, hipGetErrorString(e_));                      \
+                        "%s failed: %s", #call, hipGetErrorString(e_));                     \
+        }                                                                                   \
     } while (0)
 
 int check_dev_ptr(ovl_ctx* ctx, const void* p, const char* name) {
@@ -1378,7 +1381,6 @@ int prepare_solve(ovl_ctx* const* ctxs, int n, const int* nsrc, Work* const* w, 
         }
         const int form = ctxs[0]->form;
         if (rc != OVL_E_OOM || form == OVL_FORM_BASIS || !plan.ring) return rc;
-        (void)hipGetLastError();
         for (int i = 0; i < n; ++i) {
             ctxs[i]->r64.release();
             ctxs[i]->r32.release();

@@ -62,3 +62,25 @@ def test_solves_without_room_for_the_ring(form, precision, J, nsrc, variant, tol
     err = float((out[True] - out[False]).abs().max() / out[False].abs().max())
     print(f"form {form} precision {precision}, {J} shifts: element-wise {err:.2e}")
     assert err < tol
+
+
+# A solve that cannot fit at all returns OVL_E_OOM, leaves no HIP error for the
+# caller's next launch to find, and the context solves what fits afterwards.
+@pytest.mark.parametrize("form", [0, 1])
+def test_out_of_memory_leaves_nothing_behind(form):
+    import torch
+    from paper_2204_01583_amd import ovl
+    dims = (16, 16, 16, 16)
+    z, c = nodes(512, *CIRCLE)
+    ctx = make_ctx(dims, gauge(dims, 0.3, 6), form=form, tol=1e-10)
+    ctx.set_nodes(z, c)  # 1024 shifts x 32 sources: 412 GB of directions
+    b = torch.zeros((32, 16, 16, 16, 16, 4, 3), dtype=torch.complex128, device="cuda")
+    with pytest.raises(ovl.OvlError) as e:
+        ctx.apply_sign(b)
+    assert e.value.status == ovl.E_OOM
+    assert float(torch.ones(1000, device="cuda").mul(2).sum()) == 2000.0
+    ctx.set_nodes(z[:2], c[:2])
+    b[:1] = 1.0
+    _, st = ctx.apply_sign(b[:1])
+    assert st.n_active_end == 0
+    ctx.close()
