@@ -1398,8 +1398,9 @@ template <typename R> R* slot_ptr(const Work& w, int i) {
 int ensure_slots(ovl_ctx* ctx, Work& w, int upto, hipStream_t s) {
     const int need = std::min(upto, w.maxk) / kSlotChunk + 1;
     while ((int)ctx->slot_chunks.size() < need) {
-        ctx->slot_chunks.emplace_back();
-        HIPCHK(ctx, ctx->slot_chunks.back().ensure(ctx->slot_chunk_bytes));
+        DBuf chunk;
+        HIPCHK(ctx, chunk.ensure(ctx->slot_chunk_bytes));
+        ctx->slot_chunks.push_back(chunk);  // only memory that is there: the list is kept
     }
     w.chunks.clear();
     for (DBuf& b : ctx->slot_chunks) w.chunks.push_back(b.as<char>());

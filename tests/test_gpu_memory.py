@@ -84,3 +84,22 @@ def test_out_of_memory_leaves_nothing_behind(form):
     _, st = ctx.apply_sign(b[:1])
     assert st.n_active_end == 0
     ctx.close()
+
+
+# The basis form's slots: a chunk of 32 slots that cannot be allocated is
+# refused each time it is asked for, and a smaller solve on the same context
+# runs.  Tensors and vectors of 700 sources take 62 GB, a chunk 282 GB.
+def test_out_of_memory_in_the_basis_slots():
+    import torch
+    from paper_2204_01583_amd import ovl
+    dims, nsrc = (16, 16, 16, 16), 700
+    ctx = make_ctx(dims, gauge(dims, 0.3, 6), nq=4, form=2, tol=1e-10, maxiter=600)
+    b = torch.zeros((nsrc, 16, 16, 16, 16, 4, 3), dtype=torch.complex128, device="cuda")
+    b[0] = 1.0
+    for _ in range(2):
+        with pytest.raises(ovl.OvlError) as e:
+            ctx.apply_sign(b)
+        assert e.value.status == ovl.E_OOM
+    s, st = ctx.apply_sign(b[:1])
+    assert st.n_active_end == 0 and bool(torch.isfinite(torch.view_as_real(s)).all())
+    ctx.close()
