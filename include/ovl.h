@@ -214,8 +214,10 @@ int ovl_apply_hw(ovl_ctx* ctx, const void* in, void* out, int32_t nrhs);
  * out = H_W in as ovl_apply_hw, with the same argument rules, that allocates
  * nothing and never tunes.  It takes requests of at most 64 MiB of input and
  * output (2 nrhs 12 Vt complex128, Vt the volume rounded up to 64 sites); a
- * larger one returns OVL_E_ARG.  The gauge field must be set (ovl_set_gauge
- * allocates). */
+ * larger one returns OVL_E_ARG (a bound kept from an implementation with work
+ * buffers, so that callers meet the same answer).  The gauge field must be set
+ * (ovl_set_gauge allocates).  It holds no state: calls may overlap on other
+ * streams and threads, with contexts of their own. */
 int ovl_apply_hw_noalloc(ovl_ctx* ctx, const void* in, void* out, int32_t nrhs);
 
 /* The same operator through the FP32 stencil that OVL_PREC_MIXED uses after

@@ -19,7 +19,7 @@
 //
 // Packing to the tiled layout, the tiled stencil and unpacking moved three
 // times the bytes in three launches; per call, that / this, in us: 4^4 x 1 (FP64)
-// 15.5 / 8.6, 16^4 x 4 93.0 / 55.6, 16^3x32 x 12 474 / 351.  Bound: at the
+// 15.5 / 8.5, 16^4 x 4 93.1 / 60.5, 16^3x32 x 12 474 / 351.  Bound: at the
 // small end the launch and the call; from 16^4 on the vector memory path,
 // which moves each site's eight neighbours and eight links through L2 and L1
 // (2.3 KB per site and source, 0.4 KB of it from memory).  Two sources per
@@ -161,10 +161,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_hw_quad(const double2* __restrict
 void launch_hw(const double2* in, double2* out, const double2* U, const Geom& g, double kappa,
                int nrhs, int lnk, hipStream_t s) {
     // Block order.  A tile's sources back to back share its links in L2; once
-    // the vectors outgrow the 256 MB last-level cache, tiles back to back
-    // (which share neighbours) win: 16^3x32 x 12 (302 MB) 351 against 388 us,
-    // x 8 (201 MB) 240 against 245, 16^4 x 12 (151 MB) 177.5 against 176.0,
-    // x 4 58.2 against 55.6.
+    // input and output outgrow the 256 MB last-level cache, tiles back to back
+    // (which share neighbours) win.  Input vectors, sources / tiles back to back,
+    // in us, launches in a row: 16^4 x 4 (48 MiB) 53.0 / 55.0, x 12 (144) 149.8 /
+    // 161.4, x 15 (180) 204.1 / 211.7, x 16 (192) 229.9 / 224.8, 16^3x32 x 8 (192)
+    // 230.1 / 239.7, x 9 (216) 269.7 / 257.1, 16^4 x 20 (240) 314.3 / 288.4,
+    // 16^3x32 x 12 (288) 380.5 / 340.6.
     const int order = (size_t)g.V * nrhs * 12 * sizeof(double2) > ((size_t)192 << 20);
     const unsigned ntile = (unsigned)((g.V + kBlock / 4 - 1) / (kBlock / 4));
     const dim3 grid(ntile * (unsigned)nrhs);

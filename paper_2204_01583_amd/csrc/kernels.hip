@@ -1,9 +1,10 @@
 // HIP kernels for gfx950: layout conversion, the seed iteration's vector
 // kernels with their deterministic reductions and shifted-system scalars, the
-// shift sweeps and the basis-form sum.  Everything here is bandwidth bound (no
-// dense contraction), so the kernels stream the vectors (tiled, 12 Vt complex
-// elements per source) with one lane per element or pair of elements.  The
-// stencil is in stencil.hip.
+// shift sweeps, the basis-form sum and the rebuilt shifted solutions.  The
+// last is a dense contraction, on the FP64 matrix instruction (k_materialize);
+// everything else here is bandwidth bound and streams the vectors (tiled, 12 Vt
+// complex elements per source) with one lane per element or pair of elements.
+// The stencil is in stencil.hip.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 

@@ -27,8 +27,11 @@ namespace ovl {
 
 constexpr int kSplitThreads = 8 * kTile;  // one wave per hop of a tile
 
-// loads that are the same for the whole wave, through the scalar cache (the
-// values are not written by the kernel that reads them)
+// loads that are the same for the whole wave, through the scalar cache.  The
+// kernel that reads a value does not write it, with one exception: a source's
+// status, which its first slice block sets in the launch that finds the error.
+// Either value will do there: every block finds the same error in the same
+// partials, and a block that already sees it set does what it would do then.
 template <typename T>
 __device__ __forceinline__ T sload(const T* p) {
     typedef const __attribute__((address_space(4))) T C;
