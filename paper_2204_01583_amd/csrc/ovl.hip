@@ -675,10 +675,10 @@ static void stencil_store(ovl_ctx* ctx, int nrhs, int prec, int mode, int code) 
 // 1 FP32) and mode (0: H_W alone; 1: the solver's q_k = z_s r_k - H r_k +
 // beta q_{k-1} with its dot products, timed with every source live).  The
 // basis forms tune mode 1 inside the solve instead (tune_solver_stencil).
-// only: the choices to try, where not all of them may be taken (kept apart
-// from the free choice of the same nrhs, prec and mode).
+// only: gives the choices to try, where not all of them may be taken (kept
+// apart from the free choice of the same nrhs, prec and mode).
 static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode,
-                           const std::vector<int>* only = nullptr) {
+                           std::vector<int> (*only)(const ovl_ctx*, int) = nullptr) {
     const int nfmt = ctx->links12 ? 2 : 1;  // link formats to try: full, and two-row if SU(3)
     const char* force = getenv("OVL_STENCIL_VARIANT");
     if (force && *force) {
@@ -702,7 +702,7 @@ static int stencil_variant(ovl_ctx* ctx, int nrhs, int prec, int mode,
     const size_t es = prec ? sizeof(float2) : sizeof(double2);
     const size_t nb = (size_t)nrhs * n12(ctx) * es;
     std::vector<int> codes;
-    if (only) codes = *only;
+    if (only) codes = only(ctx, nrhs);
     else for (int c = 0; c < kStencilVariants * nfmt; ++c) codes.push_back(c);
     int best = codes[0];
     bool ok = ctx->bench_a.ensure(nb) == hipSuccess && ctx->bench_b.ensure(nb) == hipSuccess &&
@@ -1056,8 +1056,7 @@ extern "C" int ovl_apply_hw_fp32(ovl_ctx* ctx, const void* in, void* out, int32_
     HIPCHK(ctx, ctx->hw_out.ensure(nb));
     launch_pack_spinor32(static_cast<const double2*>(in), ctx->hw_in.as<float2>(), ctx->g.V, ctx->g.Vt,
                          nrhs, ctx->stream);
-    const std::vector<int> choices = hw32_choices(ctx, nrhs);
-    const int code = stencil_variant(ctx, nrhs, 1, 0, &choices);
+    const int code = stencil_variant(ctx, nrhs, 1, 0, hw32_choices);
     const int var = code % kStencilVariants, lnk = code / kStencilVariants;
     launch_wilson<float>(0, ctx->hw_in.as<float2>(), ctx->hw_out.as<float2>(),
                          stencil_links<float>(ctx, lnk), ctx->g, kappa_of(ctx->m0),
