@@ -76,7 +76,7 @@ extern "C" {
 #define OVL_FORM_FUSED     1 /* per-shift directions p_j only; s accumulated in the same sweep
                                 (both: one sweep per 16 iterations, over 16 residual buffers, or
                                 per iteration over one where the solve would take more than half of
-                                the free memory)                                             */
+                                the free memory and those buffers are over an eighth of it)   */
 #define OVL_FORM_BASIS     2 /* seed residuals r_k stored; s = sum_k h_k r_k from the scalars    */
 #define OVL_FORM_TWOPASS   3 /* as BASIS without storing the r_k: a second pass regenerates them
                                 bit for bit (deterministic reductions) and accumulates s, from 8

@@ -1154,26 +1154,34 @@ struct Plan {
 // update), but takes 15 (sweep) or 6 (two-pass) more vectors per source and
 // precision, which with a few shifts is most of the memory.  It is used where
 // the whole solve takes at most half of the memory that is free, so that a
-// solve that fits without it always fits; a solve that has its buffers asks for
-// nothing.
+// solve that fits without it always fits and leaves room for the caller's own;
+// and, where many shifts make it at most an eighth of the solve, as far as
+// everything fits with room for the residual check's and the tuner's vectors.  A
+// solve that has its buffers asks for nothing.
 Plan plan_solve(ovl_ctx* const* ctxs, int n, const int* nsrc) {
     Plan P{split_iteration(ctxs, n, nsrc), true};
     const int form = ctxs[0]->form;
     const bool sweep = form == OVL_FORM_FUSED || form == OVL_FORM_REFERENCE;
     if (!sweep && form != OVL_FORM_TWOPASS) return P;
-    double need = 0.0;
+    double need = 0.0, all = 0.0, ring = 0.0, spare = (double)((size_t)1 << 30);
     for (int i = 0; i < n; ++i) {
         const ovl_ctx* c = ctxs[i];
         const double J = (double)c->z.size(), ns = std::max(nsrc[i], 0);
         const double v64 = ns * (double)n12(c) * sizeof(double2), v32 = v64 / 2;
         const double nr = sweep ? kSweep : P.split ? 2 : kReplay, nq = P.split ? 2 : 1;
-        auto grow = [&](const DBuf& b, double bytes) { need += std::max(bytes - (double)b.bytes, 0.0); };
+        auto grow = [&](const DBuf& b, double bytes) {
+            need += std::max(bytes - (double)b.bytes, 0.0);
+            all += bytes;
+        };
+        const bool mixed = c->precision == OVL_PREC_MIXED;
+        ring += (nr - (sweep ? 1 : 2)) * (v64 + (mixed ? v32 : 0.0));
+        spare += 4.0 * v64;
         for (const DBuf* b : {&c->b64, &c->p64, &c->s64}) grow(*b, v64);
         grow(c->r64, nr * v64);
         grow(c->q64, nq * v64);
         if (sweep) grow(c->pj64, J * v64);
         if (form == OVL_FORM_REFERENCE) grow(c->xj, J * v64);
-        if (c->precision == OVL_PREC_MIXED) {
+        if (mixed) {
             grow(c->r32, nr * v32);
             grow(c->q32, nq * v32);
             if (sweep) grow(c->pj32, J * v32);
@@ -1190,7 +1198,8 @@ Plan plan_solve(ovl_ctx* const* ctxs, int n, const int* nsrc) {
             (void)hipGetLastError();
             avail = 0;
         }
-        P.ring = need <= 0.5 * (double)avail;
+        P.ring = need <= 0.5 * (double)avail ||
+                 (ring <= 0.125 * all && need + spare <= (double)avail);
     }
     // (the split iteration needs r_{k-1} beside r_k; with one buffer the
     // stencil and update kernels run)

@@ -64,6 +64,34 @@ def test_solves_without_room_for_the_ring(form, precision, J, nsrc, variant, tol
     assert err < tol
 
 
+# Many shifts: the ring is a tenth of the solve, and used as long as all of it
+# fits, beyond half of what is free.
+def test_many_shifts_keep_the_ring():
+    import torch
+    dims, J, nsrc = (16, 16, 16, 16), 130, 16
+    z, c = nodes(130, *CIRCLE)
+    b = torch.ones((nsrc, 16, 16, 16, 16, 4, 3), dtype=torch.complex128, device="cuda")
+    vec = b.numel() * 16
+    ctx = make_ctx(dims, gauge(dims, 0.3, 6), form=1, tol=1e-10, maxiter=32)
+    ctx.set_nodes(z[:J], c[:J])
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    leave = int((20 + J + 1 + 4) * vec + 1.5 * GB)
+    free = torch.cuda.mem_get_info()[0]
+    hog = torch.empty(free - leave, dtype=torch.uint8, device="cuda")
+    before = torch.cuda.mem_get_info()[0]
+    assert (20 + J) * vec > 0.5 * before
+    try:
+        ctx.apply_sign(b, allow_not_converged=True)
+        taken = before - torch.cuda.mem_get_info()[0]
+    finally:
+        hog = None  # noqa: F841
+        torch.cuda.empty_cache()
+        ctx.close()
+    print(f"taken {taken / vec:.1f} vectors")
+    assert taken > (20 + J - 0.5) * vec
+
+
 # A solve that cannot fit at all returns OVL_E_OOM, leaves no HIP error for the
 # caller's next launch to find, and the context solves what fits afterwards.
 @pytest.mark.parametrize("form", [0, 1])
